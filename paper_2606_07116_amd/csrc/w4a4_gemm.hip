@@ -295,6 +295,15 @@ hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
                             int64_t M, int64_t N, int64_t K, int log2g,
                             uint16_t* y, int64_t ldy, int32_t* acc_debug,
                             hipStream_t stream) {
+  // Few rows leave a grid of 256 x 128 tiles short of the 256 CUs, or its tiles
+  // mostly padding: small tiles with K split inside the workgroup instead
+  // (64 x 6144 x 4096, g = 128: 50 -> 12.5 us; 700 x 4096 x 14336: 168 -> 108;
+  // 64 x 28672 x 4096: 54 -> 27). Past that the large tiles, which load less,
+  // are ahead (500 x 28672 x 4096: 115 against 141).
+  const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
+  if (tiles256 <= (M <= 128 ? 256 : 128) && gemm_ksplit_supported(M, N, K, log2g))
+    return launch_w4a4_gemm_ksplit(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
+                                   log2g, y, ldy, acc_debug, stream);
   if (gemm_grouped_supported(M, N, K, log2g))
     return launch_w4a4_gemm_grouped(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N,
                                     K, log2g, y, ldy, acc_debug, stream);

@@ -110,6 +110,21 @@ def test_gemv_parts_of_k(M, N, K, g):
     _layer(M, N, K, g, seed=K + g)
 
 
+@pytest.mark.parametrize("M,N,K,g", [
+    (17, 100, 4096, 128), (32, 1000, 1024, 512),           # 32 x 16 tiles
+    (33, 4096, 640, 128), (64, 2040, 14336, 128),          # 32 x 32, fewer steps than waves; 112 groups
+    (64, 6150, 512, 256), (65, 4100, 3072, 1024),          # 64 x 32; parts of K that end inside a group
+    (32, 24580, 384, 128), (20, 24600, 1024, 1024),        # 32 x 64
+    (250, 4100, 896, 128), (100, 8200, 2048, 2048),        # 64 x 64 by eight waves
+    (333, 4096, 1536, 512), (257, 6145, 768, 256),         # 64 x 64 by four waves
+])
+def test_few_token_rows(M, N, K, g):
+    """17 to a few hundred token rows: small tiles whose waves split K, each
+    tile shape at ragged edges, with one and several groups per wave's part
+    and parts that end inside a group."""
+    _layer(M, N, K, g, seed=M + N + K)
+
+
 def test_raw_layout_and_spikes():
     _layer(150, 192, 1024, 1024, seed=5, layout="raw", n_out=6)
 
