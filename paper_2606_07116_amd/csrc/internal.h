@@ -21,7 +21,8 @@ hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
                             uint16_t* y, int64_t ldy, int32_t* acc_debug,
                             hipStream_t stream);
 
-// Several groups per row (g < K, g >= 128): MFMA GEMM with per-group fold.
+// Any number of groups per row (g >= 256): MFMA GEMM with per-group fold. The size
+// limits hold for the 6-bit kernel too.
 bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g);
 hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_scale,
                                     const int16_t* a_zero, const uint8_t* w_codes,
@@ -36,6 +37,15 @@ hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_sca
                                    const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
                                    int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                    int32_t* acc_debug, hipStream_t stream);
+
+// The 6-bit matrix format: g = 128, or one group per row on the sizes that
+// gemm_fp6_one_group says it is the faster for.
+bool gemm_fp6_one_group(int64_t M, int64_t N);
+hipError_t launch_w4a4_gemm_fp6(const uint8_t* a_codes, const uint16_t* a_scale,
+                                const int16_t* a_zero, const uint8_t* w_codes,
+                                const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
+                                int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
+                                int32_t* acc_debug, hipStream_t stream);
 
 // Decode (M <= 16) on MFMA: 16-channel row tiles, K split over 4 waves.
 bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int log2g);

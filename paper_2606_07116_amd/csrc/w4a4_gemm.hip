@@ -295,18 +295,27 @@ hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
                             int64_t M, int64_t N, int64_t K, int log2g,
                             uint16_t* y, int64_t ldy, int32_t* acc_debug,
                             hipStream_t stream) {
-  // Few rows leave a grid of 256 x 128 tiles short of the 256 CUs, or its tiles
-  // mostly padding: small tiles with K split inside the workgroup instead
-  // (64 x 6144 x 4096, g = 128: 50 -> 12.5 us; 700 x 4096 x 14336: 168 -> 108;
-  // 64 x 28672 x 4096: 54 -> 27). Past that the large tiles, which load less,
-  // are ahead (500 x 28672 x 4096: 115 against 141).
+  // Few rows leave the grid of large tiles short of the 256 CUs, or the tiles
+  // mostly padding: small tiles with K split inside the workgroup instead.
+  // At g = 128 up to 512 tiles of 64 x 64 (333 x 4096 x 14336, 384 tiles: 62 us, by
+  // 128 x 128 tiles 102; 2000 x 1000 x 8192, 512 tiles: 42 / 62; but 333 x 6144 x
+  // 4096, 576 tiles: 37 / 35, and 700 x 4096 x 14336, 704 tiles: 121 / 104). Longer
+  // groups fold less and their large tiles cost less: up to 128 of 256 x 128 (700 x
+  // 4096 x 14336, g = 512: 85 / 104; 500 x 10240 x 8192 one group: 78 / 57), twice
+  // that where half a tile's rows are padding.
+  const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
   const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
-  if (tiles256 <= (M <= 128 ? 256 : 128) && gemm_ksplit_supported(M, N, K, log2g))
+  const bool few = log2g == 7 ? tiles64 <= 512 : tiles256 <= (M <= 128 ? 256 : 128);
+  if (few && gemm_ksplit_supported(M, N, K, log2g))
     return launch_w4a4_gemm_ksplit(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
                                    log2g, y, ldy, acc_debug, stream);
-  if (gemm_grouped_supported(M, N, K, log2g))
+  if (gemm_grouped_supported(M, N, K, log2g)) {
+    if (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N)))
+      return launch_w4a4_gemm_fp6(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
+                                  log2g, y, ldy, acc_debug, stream);
     return launch_w4a4_gemm_grouped(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N,
                                     K, log2g, y, ldy, acc_debug, stream);
+  }
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const dim3 grid((unsigned)tiles), block(256);
   const bool wide = log2g >= 13;

@@ -10,20 +10,18 @@
 // group; the z * colsum terms carry the absorbed offsets).
 //
 // Organisation
-// * 8 waves per workgroup, two per SIMD.  FM = 2: waves 4 x 2, each 64 tokens
-//   x 64 channels (2 x 2 MFMA tiles of 32 x 32), workgroup tile 256 x 128,
-//   any number of groups up to GMAX.  FM = 4: waves 2 x 4, each 128 x 64,
-//   workgroup tile 256 x 256, one group per row.
+// * 8 waves per workgroup, two per SIMD: waves 4 x 2, each 64 tokens x 64
+//   channels (2 x 2 MFMA tiles of 32 x 32), workgroup tile 256 x 128.
 // * Operand unpacking (4-bit nibbles to int8 MFMA operands) is VALU work that
 //   does not overlap the MFMAs, so each packed byte is unpacked as few times
-//   as possible: the operand that four waves share (the weights for FM = 2,
-//   the activations for FM = 4) is unpacked once, when its stage is written
-//   to LDS, into two int8 planes; the other operand stays packed in LDS and
-//   is unpacked in registers by each of the two waves that read it.
+//   as possible: the weights, which four waves share, are unpacked once, when
+//   their stage is written to LDS, into two int8 planes; the activations stay
+//   packed in LDS and are unpacked in registers by each of the two waves that
+//   read them.
 // * Stages of 128 k go global memory -> registers (two or four stages ahead)
 //   -> an LDS ring of three or four slots; one LDS-only barrier per stage.
-//   16-byte chunks are XOR-swizzled by row to spread the LDS banks.  For
-//   FM = 2 the packed parts of all slots form one LDS region and the
+//   16-byte chunks are XOR-swizzled by row to spread the LDS banks.  The
+//   packed parts of all slots form one LDS region and the
 //   unpacked parts another, each addressed from one register per lane
 //   pattern with immediate offsets.
 // * Activation codes (0..15) feed the signed i8 MFMA unchanged; weight nibbles
@@ -53,16 +51,16 @@ namespace {
 
 using namespace gemm;
 
-template <int FM, bool ONEG, bool STREAM = false>
+template <bool ONEG, bool STREAM = false>
 struct GCfg {
+  static constexpr int FM = 2;                     // fragments of 32 token rows per wave
   static constexpr int THREADS = 512;              // 8 waves, 2 per SIMD
-  static constexpr int WAVES_M = FM == 2 ? 4 : 2;
+  static constexpr int WAVES_M = 4;
   static constexpr int WROWS = 32 * FM;            // token rows per wave
   static constexpr int BM = WAVES_M * WROWS;       // 256
-  static constexpr int BN = (8 / WAVES_M) * 64;    // 128 or 256
-  static constexpr bool X_IS_W = FM == 2;          // operand unpacked into LDS
-  static constexpr int P_ROWS = X_IS_W ? BM : BN;  // packed operand rows
-  static constexpr int X_ROWS = X_IS_W ? BN : BM;  // unpacked operand rows
+  static constexpr int BN = (8 / WAVES_M) * 64;    // 128
+  static constexpr int P_ROWS = BM;           // packed operand (activations) rows
+  static constexpr int X_ROWS = BN;           // unpacked operand (weights) rows
   static constexpr int P_SLOTS = P_ROWS * 4;       // 16-byte slots: 4 packed chunks per row
   static constexpr int X_SLOTS = X_ROWS * 8;       // 8 int8 chunks per row (4 x lo/hi)
   static constexpr int STAGE_SLOTS = P_SLOTS + X_SLOTS;
@@ -73,14 +71,14 @@ struct GCfg {
   // slot of every stage in a 4-stage unrolled loop is a compile-time constant)
   // (STREAM: any number of groups, their parameters staged with the stages
   // through a ring of GR entries)
-  static constexpr int GMAX = (FM == 2 && !ONEG && !STREAM) ? 28 : 1;
-  static constexpr int NBUF = (FM == 2 && (ONEG || STREAM)) ? 4 : 3;
+  static constexpr int GMAX = (!ONEG && !STREAM) ? 28 : 1;
+  static constexpr int NBUF = (ONEG || STREAM) ? 4 : 3;
   static constexpr int GR = STREAM ? 4 : 1;
   // stages held in registers between their global load and their LDS store:
   // the loads are issued NRB stages before the store (one with streamed
   // group parameters, which leaves the registers for reading fragments two
   // k-steps ahead)
-  static constexpr int NRB = (FM == 2 && ONEG) ? 4 : STREAM ? 1 : 2;
+  static constexpr int NRB = ONEG ? 4 : STREAM ? 1 : 2;
 };
 
 // packed rows: 4 chunks, swizzle c ^ (row/4 mod 4); int8 rows: 8 chunks,
@@ -92,19 +90,19 @@ __device__ __forceinline__ int xslot(int row, int c) { return row * 8 + (c ^ ((r
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned int gemm_u32x4 __attribute__((ext_vector_type(4)));
 
-// MODE: stages per group: 1, 2, 4, or a multiple of 8 (MODE 8).  ONEG: one
+// MODE: stages per group: 2, 4, or a multiple of 8 (MODE 8).  ONEG: one
 // group per row (g = K).  STREAM: several groups, any number of them: each
 // group's parameters travel with its stages (row scales and zero-points of
 // the tile's rows, column sums of its columns) through a small LDS ring, and
 // its zero-point term is applied right after its fold, in pairs of groups.
-template <bool DBG, int MODE, int FM, bool ONEG, bool STREAM>
+template <bool DBG, int MODE, bool ONEG, bool STREAM>
 __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
     const uint8_t* __restrict__ A, const uint16_t* __restrict__ a_scale,
     const int16_t* __restrict__ a_zero, const uint8_t* __restrict__ W,
     const uint16_t* __restrict__ w_scale, const int32_t* __restrict__ w_colsum, int M, int N,
     int K, int log2g, uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_dbg) {
-  using C = GCfg<FM, ONEG, STREAM>;
-  constexpr bool XW = C::X_IS_W;
+  using C = GCfg<ONEG, STREAM>;
+  constexpr int FM = C::FM;
   __shared__ uint4 ring[C::NBUF * C::STAGE_SLOTS];
   // per group b: s / 16 and z of the tile's rows, colsum of its columns
   __shared__ float sRS[C::GMAX][C::BM];
@@ -133,19 +131,18 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   const int G = K >> log2g;
   const int spg = 1 << (log2g - 7);  // stages per group
 
-  // LDS addressing.  FM = 2: the packed parts of all ring slots form one
+  // LDS addressing.  The packed parts of all ring slots form one
   // region and the unpacked parts another (each at most 64 KB), and every
   // lane pattern (row, swizzled chunk) has one element index, region start
   // included, computed once and hidden from the optimiser: slot and fragment
   // offsets then stay within the 16-bit immediate of ds_read / ds_write,
   // and the loop holds one address register per pattern.  (Folded into
   // per-slot addresses, slots beyond 64 KB each took a register of their
-  // own.)  FM = 4: slot s holds its packed then its unpacked part.
-  constexpr bool SPLIT = FM == 2;
-  constexpr int PBASE = 0, XBASE = SPLIT ? C::NBUF * C::P_SLOTS : C::P_SLOTS;
-  constexpr int PSTEP = SPLIT ? C::P_SLOTS : C::STAGE_SLOTS;  // slot stride, packed part
-  constexpr int XSTEP = SPLIT ? C::X_SLOTS : C::STAGE_SLOTS;  // slot stride, unpacked part
-  static_assert(!SPLIT || (C::NBUF * C::P_SLOTS * 16 <= 65536 && C::NBUF * C::X_SLOTS * 16 <= 65536),
+  // own.)
+  constexpr int PBASE = 0, XBASE = C::NBUF * C::P_SLOTS;
+  constexpr int PSTEP = C::P_SLOTS;  // slot stride, packed part
+  constexpr int XSTEP = C::X_SLOTS;  // slot stride, unpacked part
+  static_assert(C::NBUF * C::P_SLOTS * 16 <= 65536 && C::NBUF * C::X_SLOTS * 16 <= 65536,
                 "each region within one 16-bit LDS offset");
   auto opaque = [](int v) __attribute__((always_inline)) {
     asm volatile("" : "+v"(v));
@@ -156,12 +153,12 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   // s % 4 (16 bytes = 32 k); rows past M (N) read as zero.  Activation rows
   // are row-major (stride K / 2); the weights are in the blocked layout, where
   // a stage of a row is 64 bytes of a 1 KB block of 16 rows.
-  const uint8_t* pbase = XW ? A + (int64_t)tm * ldk : W + (int64_t)tn * ldk;
-  const uint8_t* xbase = XW ? W + (int64_t)tn * ldk : A + (int64_t)tm * ldk;
+  const uint8_t* pbase = A + (int64_t)tm * ldk;
+  const uint8_t* xbase = W + (int64_t)tn * ldk;
   // (weights: bands of 16 rows of the blocked layout, K a multiple of 128, so a
   // band is 16 ldk bytes; the padding rows of the last band hold zero codes)
   const int wrows = (N - tn + 15) & ~15;
-  const int prows = XW ? M - tm : wrows, xrows = XW ? wrows : M - tm;
+  const int prows = M - tm, xrows = wrows;
   const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
       (void*)pbase, 0, (int)((int64_t)prows * ldk), 0x00020000);
   const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -172,7 +169,7 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   const int crow = tid >> 2, cch = tid & 3;
   const int voff_a = crow * (int)ldk + cch * 16;
   const int voff_w = (crow >> 4) * 16 * (int)ldk + (crow & 15) * 64 + cch * 16;
-  const int pvoff = XW ? voff_a : voff_w, xvoff = XW ? voff_w : voff_a;
+  const int pvoff = voff_a, xvoff = voff_w;
   const int vstep = (C::THREADS / 4) * (int)ldk;  // 128 rows (8 weight bands)
   constexpr int NLD = C::P_LD + C::X_LD;
   v4i rgb[C::NRB][NLD];   // stages in flight
@@ -183,7 +180,7 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
     const __amdgpu_buffer_rsrc_t pr = ok ? prsrc : prsrc0, xr = ok ? xrsrc : xrsrc0;
     // a stage is 64 bytes of an activation row, one 1 KB block of a weight band
     const int soff = ok ? st * (C::KSTAGE / 2) : 0;
-    const int psoff = XW ? soff : 16 * soff, xsoff = XW ? 16 * soff : soff;
+    const int psoff = soff, xsoff = 16 * soff;
 #pragma unroll
     for (int i = 0; i < C::P_LD; ++i)
       rg[i] = __builtin_amdgcn_raw_buffer_load_b128(pr, pvoff + i * vstep, psoff, 0);
@@ -193,38 +190,20 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   };
   // element index of this thread's chunk in slot 0 (row crow + 128 i adds
   // 512 i packed / 1024 i unpacked slots: the swizzles repeat every 128 rows)
-  const int ps_idx = SPLIT ? opaque(PBASE + pslot(crow, cch)) : 0;
-  const int xs_idx0 = SPLIT ? opaque(XBASE + xslot(crow, 2 * cch)) : 0;
-  const int xs_idx1 = SPLIT ? opaque(XBASE + xslot(crow, 2 * cch + 1)) : 0;
+  const int ps_idx = opaque(PBASE + pslot(crow, cch));
+  const int xs_idx0 = opaque(XBASE + xslot(crow, 2 * cch));
+  const int xs_idx1 = opaque(XBASE + xslot(crow, 2 * cch + 1));
   auto lstore_p = [&](int slot, const v4i (&rg)[NLD]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < C::P_LD; ++i) {
-      if constexpr (SPLIT)
-        ring[ps_idx + slot * PSTEP + 512 * i] = __builtin_bit_cast(uint4, rg[i]);
-      else
-        ring[slot * PSTEP + pslot(crow + 128 * i, cch)] = __builtin_bit_cast(uint4, rg[i]);
-    }
+    for (int i = 0; i < C::P_LD; ++i)
+      ring[ps_idx + slot * PSTEP + 512 * i] = __builtin_bit_cast(uint4, rg[i]);
   };
   auto lstore_x = [&](int slot, const v4i (&rg)[NLD]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < C::X_LD; ++i) {
       const uint4 d = __builtin_bit_cast(uint4, rg[C::P_LD + i]);
-      v4i lo, hi;
-      if constexpr (XW) {
-        lo = wgt_lo16(d);
-        hi = wgt_hi16(d);
-      } else {
-        lo = act_lo(d);
-        hi = act_hi(d);
-      }
-      if constexpr (SPLIT) {
-        ring[xs_idx0 + slot * XSTEP + 1024 * i] = __builtin_bit_cast(uint4, lo);
-        ring[xs_idx1 + slot * XSTEP + 1024 * i] = __builtin_bit_cast(uint4, hi);
-      } else {
-        uint4* X = ring + slot * XSTEP + XBASE;
-        X[xslot(crow + 128 * i, 2 * cch)] = __builtin_bit_cast(uint4, lo);
-        X[xslot(crow + 128 * i, 2 * cch + 1)] = __builtin_bit_cast(uint4, hi);
-      }
+      ring[xs_idx0 + slot * XSTEP + 1024 * i] = __builtin_bit_cast(uint4, wgt_lo16(d));
+      ring[xs_idx1 + slot * XSTEP + 1024 * i] = __builtin_bit_cast(uint4, wgt_hi16(d));
     }
   };
   auto lstore = [&](int slot, const v4i (&rg)[NLD]) __attribute__((always_inline)) {
@@ -281,34 +260,26 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   // fragments (one 16-byte chunk each) and, per plane pl, its unpacked
   // fragments; lane row fr, fragment f is 32 rows further (which keeps both
   // swizzles).
-  constexpr int NPF = XW ? FM : 2;  // packed fragments per wave
-  constexpr int NXF = XW ? 2 : FM;  // unpacked fragments per wave
-  const int prow0 = (XW ? wm * C::WROWS : wn * 64) + fr;
-  const int xrow0 = (XW ? wn * 64 : wm * C::WROWS) + fr;
+  constexpr int NPF = FM;  // packed fragments per wave
+  constexpr int NXF = 2;   // unpacked fragments per wave
+  const int prow0 = wm * C::WROWS + fr;
+  const int xrow0 = wn * 64 + fr;
   // element indices of the lane's fragments in slot 0, per chunk column
-  int pr_idx[2] = {}, xr_idx[4] = {};
-  if constexpr (SPLIT) {
+  int pr_idx[2], xr_idx[4];
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) pr_idx[jj] = opaque(PBASE + pslot(prow0, 2 * h + jj));
+  for (int jj = 0; jj < 2; ++jj) pr_idx[jj] = opaque(PBASE + pslot(prow0, 2 * h + jj));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) xr_idx[q] = opaque(XBASE + xslot(xrow0, 4 * h + q));
-  }
+  for (int q = 0; q < 4; ++q) xr_idx[q] = opaque(XBASE + xslot(xrow0, 4 * h + q));
   auto pread = [&](int slot, int jj, uint4 (&pp)[NPF]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int f = 0; f < NPF; ++f) {
-      if constexpr (SPLIT) pp[f] = ring[pr_idx[jj] + slot * PSTEP + f * 32 * 4];
-      else pp[f] = ring[slot * PSTEP + pslot(prow0, 2 * h + jj) + f * 32 * 4];
-    }
+    for (int f = 0; f < NPF; ++f) pp[f] = ring[pr_idx[jj] + slot * PSTEP + f * 32 * 4];
   };
   auto xread = [&](int slot, int jj, int pl, uint4 (&px)[NXF]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int f = 0; f < NXF; ++f) {
-      if constexpr (SPLIT) px[f] = ring[xr_idx[2 * jj + pl] + slot * XSTEP + f * 32 * 8];
-      else px[f] = ring[slot * XSTEP + XBASE + xslot(xrow0, 4 * h + 2 * jj + pl) + f * 32 * 8];
-    }
+    for (int f = 0; f < NXF; ++f) px[f] = ring[xr_idx[2 * jj + pl] + slot * XSTEP + f * 32 * 8];
   };
 
-  // With one group per row (the only case of FM = 4) F is first written by
+  // With one group per row F is first written by
   // the single fold after the loop, so it takes no registers during it.
   constexpr bool SINGLE = ONEG;
   v16i acc[FM][2];
@@ -373,32 +344,13 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
       __attribute__((always_inline)) {
     constexpr bool HI = decltype(PL)::value;
     constexpr bool FRESH = decltype(FC)::value;
-    if constexpr (XW) {  // activations packed, weights unpacked
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm) {
-        const v4i ua = HI ? act_hi(pp[fm]) : act_lo(pp[fm]);
+    for (int fm = 0; fm < FM; ++fm) {
+      const v4i ua = HI ? act_hi(pp[fm]) : act_lo(pp[fm]);
 #pragma unroll
-        for (int fn = 0; fn < 2; ++fn)
-          acc[fm][fn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-              __builtin_bit_cast(v4i, px[fn]), ua, FRESH ? v16i{} : acc[fm][fn], 0, 0, 0);
-      }
-    } else {  // weights packed, activations unpacked
-#pragma unroll
-      for (int fn = 0; fn < 2; ++fn) {
-        const v4i ub = HI ? wgt_hi16(pp[fn]) : wgt_lo16(pp[fn]);
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm)
-          acc[fm][fn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-              ub, __builtin_bit_cast(v4i, px[fm]), FRESH ? v16i{} : acc[fm][fn], 0, 0, 0);
-      }
-    }
-    if constexpr (FM == 4) {
-      // keep the 128 accumulators in accumulation registers (an empty asm
-      // with AGPR operands), leaving the vector registers to the pipeline
-#pragma unroll
-      for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-        for (int fn = 0; fn < 2; ++fn) asm volatile("" : "+a"(acc[fm][fn]));
+      for (int fn = 0; fn < 2; ++fn)
+        acc[fm][fn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+            __builtin_bit_cast(v4i, px[fn]), ua, FRESH ? v16i{} : acc[fm][fn], 0, 0, 0);
     }
   };
   auto dump = [&](int b) __attribute__((always_inline)) {  // debug: raw accumulators of group b
@@ -483,13 +435,12 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   lstore(1, rb);
   lstore_g(1, gqa1);
   lds_barrier();
-  // FM = 2 reads each k-step's unpacked fragments two k-steps ahead (xa, xb,
-  // x2, x3 hold k-steps 0..3 of a stage).
-  constexpr bool PF2 = FM == 2;
+  // Each k-step's unpacked fragments are read two k-steps ahead (xa, xb, x2, x3
+  // hold k-steps 0..3 of a stage).
   uint4 pa[NPF], pb[NPF], xa[NXF], xb[NXF], x2[NXF], x3[NXF];
   pread(0, 0, pa);
   xread(0, 0, 0, xa);
-  if constexpr (PF2) xread(0, 0, 1, xb);
+  xread(0, 0, 1, xb);
 
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -528,43 +479,24 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
       lstore_g(st + 2, gq);
       gload_g(st + 2 + C::NRB, gq);
     }
-    if constexpr (PF2) {  // on entry pa, xa (k-step 0) and xb (k-step 1) are loaded
-      pread(slot, 1, pb);
-      xread(slot, 1, 0, x2);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pa, xa, LO{}, FC);
-      xread(slot, 1, 1, x3);
-      lstore_p(slot_of(2), rg);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pa, xb, HI{}, LO{});
-      pread(slot_of(1), 0, pa);  // past the last stage: stale, unused
-      xread(slot_of(1), 0, 0, xa);
-      lstore_x(slot_of(2), rg);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pb, x2, LO{}, LO{});
-      xread(slot_of(1), 0, 1, xb);
-      gload(st + 2 + C::NRB, rg);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pb, x3, HI{}, LO{});
-    } else {  // FM = 4 (one group); on entry pa, xa (k-step 0) are loaded
-      xread(slot, 0, 1, xb);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pa, xa, LO{}, FC);
-      pread(slot, 1, pb);
-      xread(slot, 1, 0, xa);
-      lstore_p(slot_of(2), rg);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pa, xb, HI{}, LO{});
-      xread(slot, 1, 1, xb);
-      lstore_x(slot_of(2), rg);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pb, xa, LO{}, LO{});
-      pread(slot_of(1), 0, pa);  // past the last stage: stale, unused
-      xread(slot_of(1), 0, 0, xa);
-      gload(st + 2 + C::NRB, rg);
-      __builtin_amdgcn_sched_barrier(0);
-      mma1(pb, xb, HI{}, LO{});
-    }
+    // on entry pa, xa (k-step 0) and xb (k-step 1) are loaded
+    pread(slot, 1, pb);
+    xread(slot, 1, 0, x2);
+    __builtin_amdgcn_sched_barrier(0);
+    mma1(pa, xa, LO{}, FC);
+    xread(slot, 1, 1, x3);
+    lstore_p(slot_of(2), rg);
+    __builtin_amdgcn_sched_barrier(0);
+    mma1(pa, xb, HI{}, LO{});
+    pread(slot_of(1), 0, pa);  // past the last stage: stale, unused
+    xread(slot_of(1), 0, 0, xa);
+    lstore_x(slot_of(2), rg);
+    __builtin_amdgcn_sched_barrier(0);
+    mma1(pb, x2, LO{}, LO{});
+    xread(slot_of(1), 0, 1, xb);
+    gload(st + 2 + C::NRB, rg);
+    __builtin_amdgcn_sched_barrier(0);
+    mma1(pb, x3, HI{}, LO{});
     if constexpr (decltype(LC)::value) {  // the group's last stage
       const int b = st >> (log2g - 7);
       if constexpr (DBG) {
@@ -592,17 +524,7 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
   using T = std::true_type;
   using Fl = std::false_type;
   int st = 0;
-  if constexpr (MODE == 1) {  // every stage is a group
-    for (; st + 4 <= nst; st += 4) {
-      body(I0{}, T{}, T{}, st, PN{});
-      body(I1{}, T{}, T{}, st + 1, PN{});
-      body(I2{}, T{}, T{}, st + 2, PN{});
-      body(I3{}, T{}, T{}, st + 3, PN{});
-    }
-    if (st < nst) body(I0{}, T{}, T{}, st, PN{});
-    if (st + 1 < nst) body(I1{}, T{}, T{}, st + 1, PN{});
-    if (st + 2 < nst) body(I2{}, T{}, T{}, st + 2, PN{});
-  } else if constexpr (MODE == 2) {  // groups of two stages
+  if constexpr (MODE == 2) {  // groups of two stages
     for (; st + 4 <= nst; st += 4) {
       body(I0{}, T{}, Fl{}, st, PN{});
       body(I1{}, Fl{}, T{}, st + 1, PN{});
@@ -722,20 +644,20 @@ bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g) {
          256 * G * 2 < (int64_t(1) << 31);
 }
 
-template <int FM, bool ONEG, bool STREAM = false>
+template <bool ONEG, bool STREAM = false>
 hipError_t launch_g(const uint8_t* a_codes, const uint16_t* a_scale, const int16_t* a_zero,
                     const uint8_t* w_codes, const uint16_t* w_scale, const int32_t* w_colsum,
                     int64_t M, int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                     int32_t* acc_debug, hipStream_t stream) {
-  using C = GCfg<FM, ONEG, STREAM>;
+  using C = GCfg<ONEG, STREAM>;
   const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
   const dim3 grid((unsigned)tiles), block(C::THREADS);
 #define OFFQ_GG(D, MD)                                                                        \
-  hipLaunchKernelGGL((w4a4_gemm_grouped_kernel<D, MD, FM, ONEG, STREAM>), grid, block, 0, stream, a_codes,  \
+  hipLaunchKernelGGL((w4a4_gemm_grouped_kernel<D, MD, ONEG, STREAM>), grid, block, 0, stream, a_codes,  \
                      a_scale, a_zero, w_codes, w_scale, w_colsum, (int)M, (int)N, (int)K, log2g, \
                      y, ldy, acc_debug)
 #define OFFQ_GG_M(D)                                                                 \
-  if (log2g == 7) OFFQ_GG(D, 1); else if (log2g == 8) OFFQ_GG(D, 2);                \
+  if (log2g == 8) OFFQ_GG(D, 2);                                                    \
   else if (log2g == 9) OFFQ_GG(D, 4); else OFFQ_GG(D, 8);
   // A debug request runs an accumulator-only pass, then the regular kernel.
   if (acc_debug) { OFFQ_GG_M(true) }
@@ -750,21 +672,15 @@ hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_sc
                                     const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
                                     int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                     int32_t* acc_debug, hipStream_t stream) {
-  // one group per row and enough 256 x 256 tiles to fill the chip: the wider
-  // wave tiles
-  const bool wide = (K >> log2g) == 1 && ((M + 255) / 256) * ((N + 255) / 256) >= 384;
-  if (wide)
-    return launch_g<4, true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
-                             y, ldy, acc_debug, stream);
   if ((K >> log2g) == 1)
-    return launch_g<2, true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
+    return launch_g<true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
                              y, ldy, acc_debug, stream);
   // several groups: the parameters of up to 28 groups sit in LDS for the whole
   // tile; more groups stream theirs with the stages
-  if ((K >> log2g) > GCfg<2, false>::GMAX)
-    return launch_g<2, false, true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
+  if ((K >> log2g) > GCfg<false>::GMAX)
+    return launch_g<false, true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
                                     log2g, y, ldy, acc_debug, stream);
-  return launch_g<2, false>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
+  return launch_g<false>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
                             y, ldy, acc_debug, stream);
 }
 

@@ -125,6 +125,20 @@ def test_few_token_rows(M, N, K, g):
     _layer(M, N, K, g, seed=M + N + K)
 
 
+@pytest.mark.parametrize("M,N,K,g", [
+    (641, 6150, 128, 128), (1100, 3000, 384, 128),         # g = 128, 128 x 128 tiles: one, three stages
+    (1030, 4098, 640, 128), (513, 8200, 4096, 128),
+    (4096, 4096, 256, 128), (4001, 4090, 640, 128),        # g = 128, 256 x 256 tiles
+    (4000, 4000, 1024, 1024), (3841, 4090, 512, 512),      # one group, 256 x 256 tiles
+    (2040, 4090, 512, 512), (1800, 5000, 2048, 2048),      # one group, 256 x 128 tiles
+    (1500, 6150, 8192, 256), (1300, 6200, 7936, 256),      # 32 and 31 groups of 256, streamed
+])
+def test_large_tile_forms(M, N, K, g):
+    """Each large-tile kernel at ragged edges, with the smallest and odd stage
+    counts."""
+    _layer(M, N, K, g, seed=M + N + K)
+
+
 def test_raw_layout_and_spikes():
     _layer(150, 192, 1024, 1024, seed=5, layout="raw", n_out=6)
 
