@@ -541,45 +541,116 @@ __global__ __launch_bounds__(256) void rotation_kernel(const double* __restrict_
   for (int c = tid; c < D; c += 256) R[r * ldR + c] = (float)(row[c] * scale);
 }
 
-// W_out = W R (fp32; 64 x 64 output tiles, 4 x 4 per thread, k slices of 16).
-__global__ __launch_bounds__(256) void fuse_gemm_kernel(const float* __restrict__ W, int64_t ldW,
-                                                        int N, int K, const float* __restrict__ R,
-                                                        int64_t ldR, float* __restrict__ Wo,
-                                                        int64_t ldo) {
-  __shared__ float As[16][65], Bs[16][64];
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int n0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = tid; e < 16 * 64; e += 256) {
-      const int rr = e >> 4, kk = e & 15;   // W tile: 64 rows x 16 k
-      const int n = n0 + rr, k = k0 + kk;
-      As[kk][rr] = (n < N && k < K) ? W[(int64_t)n * ldW + k] : 0.0f;
-      const int kb = e >> 6, cb = e & 63;   // R tile: 16 k x 64 columns
-      Bs[kb][cb] = (k0 + kb < K && c0 + cb < K) ? R[(int64_t)(k0 + kb) * ldR + c0 + cb] : 0.0f;
+// Wo = W R in fp32 on the matrix cores (v_mfma_f32_32x32x2_f32, fp32 products and
+// sums): these run at twice the rate of vector FMAs, which bounded a 64 x 64 tile of
+// them (6144 x 4096 x 4096: 65 TFLOP/s of the vector units' 79). A workgroup of four
+// waves owns 64 TW x 64 TW outputs; slices of 32 k go through registers into one of
+// two LDS buffers. The k-order of the matrix instructions is free as long as both
+// operands share it: a lane half takes four consecutive k of every eight, so that a
+// W fragment is one 16-byte LDS read. W rows are XOR-swizzled and R rows padded to
+// spread the LDS banks.
+typedef float fuse_v16f __attribute__((ext_vector_type(16)));
+
+template <int TW>
+__global__ __launch_bounds__(256, 2) void fuse_gemm_kernel(const float* __restrict__ W, int64_t ldW,
+                                                           int N, int K, const float* __restrict__ R,
+                                                           int64_t ldR, float* __restrict__ Wo,
+                                                           int64_t ldo, int vec) {
+  constexpr int T = 64 * TW, BK = 32, LB = T + 8;
+  constexpr int NA = T / 32, NB = T / 32;  // float4 of each operand per thread and slice
+  constexpr int BROWS = 1024 / T;          // R rows loaded at a time
+  __shared__ __attribute__((aligned(16))) float4 As[2][T * 8];
+  __shared__ __attribute__((aligned(16))) float Bs[2][BK * LB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int h = lane >> 5, fr = lane & 31;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int n0 = blockIdx.y * T, c0 = blockIdx.x * T;
+  const int ar = tid >> 3, ac = tid & 7;                  // W: row, group of 4 k
+  const int br = tid / (T / 4), bc = (tid % (T / 4)) * 4;  // R: row k, first of 4 columns
+
+  // four consecutive floats of a row, zero past its n valid ones
+  auto load4 = [&](const float* row, int at, int n, bool ok) {
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (ok) {
+      if (vec && at + 4 <= n) {
+        v = *reinterpret_cast<const float4*>(row + at);
+      } else {
+        if (at < n) v.x = row[at];
+        if (at + 1 < n) v.y = row[at + 1];
+        if (at + 2 < n) v.z = row[at + 2];
+        if (at + 3 < n) v.w = row[at + 3];
+      }
     }
-    __syncthreads();
+    return v;
+  };
+  float4 ra[NA], rb[NB];
+  auto gload = [&](int k0) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
+    for (int i = 0; i < NA; ++i) {
+      const int n = n0 + ar + 32 * i;
+      ra[i] = load4(W + (int64_t)n * ldW, k0 + 4 * ac, K, n < N);
+    }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = As[k][ty * 4 + u];
-        b[u] = Bs[k][tx * 4 + u];
+    for (int i = 0; i < NB; ++i) {
+      const int k = k0 + br + BROWS * i;
+      rb[i] = load4(R + (int64_t)k * ldR, c0 + bc, K, k < K);
+    }
+  };
+  auto lstore = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int r = ar + 32 * i;
+      As[buf][r * 8 + (ac ^ ((r >> 1) & 7))] = ra[i];
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      *reinterpret_cast<float4*>(&Bs[buf][(br + BROWS * i) * LB + bc]) = rb[i];
+  };
+
+  fuse_v16f acc[TW][TW];
+#pragma unroll
+  for (int a = 0; a < TW; ++a)
+#pragma unroll
+    for (int b = 0; b < TW; ++b) acc[a][b] = fuse_v16f{};
+  gload(0);
+  lstore(0);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < K; k0 += BK, buf ^= 1) {
+    if (k0 + BK < K) gload(k0 + BK);
+#pragma unroll
+    for (int i = 0; i < BK / 8; ++i) {
+      float a[TW][4], b[TW][4];
+#pragma unroll
+      for (int t = 0; t < TW; ++t) {
+        const int r = (wm * TW + t) * 32 + fr;
+        const float4 v = As[buf][r * 8 + ((2 * i + h) ^ ((r >> 1) & 7))];
+        a[t][0] = v.x, a[t][1] = v.y, a[t][2] = v.z, a[t][3] = v.w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[t][j] = Bs[buf][(8 * i + 4 * h + j) * LB + (wn * TW + t) * 32 + fr];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = __builtin_fmaf(a[u], b[v], acc[u][v]);
+        for (int t = 0; t < TW; ++t)
+#pragma unroll
+          for (int u = 0; u < TW; ++u)
+            acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t][j], b[u][j], acc[t][u], 0, 0, 0);
     }
+    if (k0 + BK < K) lstore(buf ^ 1);
     __syncthreads();
   }
+  // register i of (t, u): row 8 (i / 4) + 4 h + i % 4, column fr of its 32 x 32
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int t = 0; t < TW; ++t)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int n = n0 + ty * 4 + u, c = c0 + tx * 4 + v;
-      if (n < N && c < K) Wo[(int64_t)n * ldo + c] = acc[u][v];
+    for (int u = 0; u < TW; ++u) {
+      const int c = c0 + (wn * TW + u) * 32 + fr;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int n = n0 + (wm * TW + t) * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+        if (n < N && c < K) Wo[(int64_t)n * ldo + c] = acc[t][u][i];
+      }
     }
 }
 
@@ -716,8 +787,20 @@ hipError_t launch_build_rotation(const double* U, int64_t ldU, int64_t D, const 
 
 hipError_t launch_fuse_weights(const float* W, int64_t ldW, int64_t N, int64_t K, const float* R,
                                int64_t ldR, float* Wo, int64_t ldo, hipStream_t stream) {
-  hipLaunchKernelGGL(fuse_gemm_kernel, dim3((unsigned)((K + 63) / 64), (unsigned)((N + 63) / 64)),
-                     dim3(256), 0, stream, W, ldW, (int)N, (int)K, R, ldR, Wo, ldo);
+  // 16-byte loads where every row starts on 16 bytes
+  const int vec = ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(R)) & 15) == 0 &&
+                  ldW % 4 == 0 && ldR % 4 == 0;
+  // 128 x 128 tiles, two workgroups per CU, unless a last partial round costs more
+  // than the 64 x 64 tiles' lower rate: 287 us a round of 512 against 0.656 us a tile
+  // at K = 2048 (3000 rows, 384 tiles: 287 / 252 us; 4000 rows, 512: 287 / 322)
+  const int64_t tiles = ((N + 127) / 128) * ((K + 127) / 128);
+#define OFFQ_FUSE(TW)                                                                            \
+  hipLaunchKernelGGL(fuse_gemm_kernel<TW>,                                                       \
+                     dim3((unsigned)((K + 64 * TW - 1) / (64 * TW)),                             \
+                          (unsigned)((N + 64 * TW - 1) / (64 * TW))),                            \
+                     dim3(256), 0, stream, W, ldW, (int)N, (int)K, R, ldR, Wo, ldo, vec)
+  if ((tiles + 511) / 512 * 437 <= tiles) OFFQ_FUSE(2); else OFFQ_FUSE(1);
+#undef OFFQ_FUSE
   return hipGetLastError();
 }
 

@@ -153,6 +153,24 @@ def test_fuse_and_permute_weights(N, K):
     assert np.array_equal(Wp, OC.permute_rows(W, perm))
 
 
+@pytest.mark.parametrize("N,K,off", [(1, 1, 0), (65, 130, 0), (33, 1001, 0), (200, 256, 1),
+                                     (9000, 770, 0), (8960, 772, 0)])
+def test_fuse_weights_tiles(N, K, off):
+    """Both tile sizes (the last two on 128 x 128) at ragged edges, rows on and off
+    16-byte boundaries: every element within the bound of a K-term fp32 sum."""
+    rng = np.random.default_rng(N + K)
+    W = rng.standard_normal((N, K)).astype(np.float32)
+    R = (rng.standard_normal((K, K)) / np.sqrt(K)).astype(np.float32)
+    big = torch.zeros((N, K + 8 + off), dtype=torch.float32, device=P.DEV)
+    Wd = big[:, off:off + K]
+    Wd.copy_(torch.from_numpy(W))
+    got = P.host(offq.offq_fuse_weights(Wd, torch.from_numpy(R).to(P.DEV)))
+    torch.cuda.synchronize()
+    W64, R64 = W.astype(np.float64), R.astype(np.float64)
+    bound = (K + 2) * 2.0 ** -24 * (np.abs(W64) @ np.abs(R64))
+    assert np.all(np.abs(got - W64 @ R64) <= bound)
+
+
 def test_calibration_pipeline_moves_the_outlier_to_the_group_heads():
     """top-1 selection -> covariance -> eigh -> grouping -> rotation on the GPU
     for one 512-channel layer input with one shared outlier direction: the
