@@ -175,10 +175,16 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void w4a4_gemm_fp6_kernel(
     t = (int)__builtin_amdgcn_udot8(c.z, 0x11111111u, t, false);
     t = (int)__builtin_amdgcn_udot8(c.w, 0x11111111u, t, false);
     asum[i] = t;
-    // the row's four chunks (quad_perm [1, 0, 3, 2], then [2, 3, 0, 1])
-    t += __builtin_amdgcn_update_dpp(0, t, 0xB1, 0xF, 0xF, true);
-    t += __builtin_amdgcn_update_dpp(0, t, 0x4E, 0xF, 0xF, true);
-    pT[buf][0][srow + RS * i] = 0.125f * (float)t;
+  };
+  auto put_sums = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < ASETS; ++i) {
+      // the row's four chunks (quad_perm [1, 0, 3, 2], then [2, 3, 0, 1])
+      int t = asum[i];
+      t += __builtin_amdgcn_update_dpp(0, t, 0xB1, 0xF, 0xF, true);
+      t += __builtin_amdgcn_update_dpp(0, t, 0x4E, 0xF, 0xF, true);
+      pT[buf][0][srow + RS * i] = 0.125f * (float)t;
+    }
   };
   auto put_w = [&](int buf, int i, const uint4& c) __attribute__((always_inline)) {
     const uint32_t X = 0x88888888u;
@@ -194,6 +200,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void w4a4_gemm_fp6_kernel(
     for (int i = 0; i < ASETS; ++i) put_a(buf, i, r.a[i]);
 #pragma unroll
     for (int i = 0; i < WSETS; ++i) put_w(buf, i, r.w[i]);
+    put_sums(buf);
     put_p(buf, r);
   };
 
@@ -277,7 +284,10 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void w4a4_gemm_fp6_kernel(
         else put_w(buf ^ 1, q - ASETS, nxt.w[q >= ASETS ? q - ASETS : 0]);
       }
       if (fm == FM - 1) {
-        put_p(buf ^ 1, nxt);
+        if (FOLD == 1 || st + 1 == nst - 1) {  // (one group: its last stage carries them)
+          put_sums(buf ^ 1);
+          put_p(buf ^ 1, nxt);
+        }
         gload(st + 1 + NSET, nxt);
       }
     };
