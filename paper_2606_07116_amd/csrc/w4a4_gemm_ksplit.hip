@@ -1,5 +1,6 @@
-// W4A4 GEMM for a few hundred token rows (gfx950, v_mfma_i32_16x16x64_i8): the
-// shapes whose 256 x 128 output tiles would leave most of the chip idle.
+// W4A4 GEMM for one to a few hundred token rows (gfx950, v_mfma_i32_16x16x64_i8):
+// decode steps, and the shapes whose large output tiles would leave most of the
+// chip idle.
 //
 //   acc_b[m,n] = sum_{k in group b} q_a[m,k] q_w[n,k]                 (int32)
 //   Y[m,n]     = sw[n] * sum_b s[m,b] * (acc_b[m,n] - z[m,b] * colsum[b,n])
@@ -279,8 +280,24 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //   32 x 32 tiles by 16 waves up to 256 of them (64 x 4096 x 14336: 19.3; 64 x 32 by
 //     8 waves 31), 32 x 16 by 8 waves up to 64 (17 x 1024 x 4096: 6.4 / 7.3);
 //   64 x 32 tiles by 8 waves between (64 x 6144 x 4096: 12.5; 32 x 32 tiles 14.1).
+// Up to 16 rows the weights' stream bounds it, and waves in flight (per byte) carry
+// it; the activations are read again by every channel tile, which counts from about
+// five rows:
+//   narrow outputs 16 channels by 8 waves, by 16 from K = 8192 (16 x 4096 x 4096: 5.2;
+//     1 x 4096 x 14336: 9.2, by 8 waves 10.5);
+//   wider ones with M <= 4 the same by 8 waves, by 4 from N = 16384 (1 x 10240 x 8192:
+//     11.4; 1 x 28672 x 4096: 13.5, by 8 waves 15.1);
+//   with more rows 32 channels by 16 waves (16 x 14336 x 4096: 10.2; 16 channels by 8
+//     waves 11.5), from N = 16384 by 4 waves where K is short (16 x 28672 x 4096: 16.3 /
+//     16.8), 64 channels by 8 where it is longer (16 x 28672 x 8192: 23.5 / 24.3).
 struct KsShape { int mt, t, p; };
-KsShape ks_shape(int64_t M, int64_t N) {
+KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
+  if (M <= 16) {
+    if (N < 6144) return {1, 1, K >= 8192 ? 16 : 8};
+    if (M <= 4) return {1, 1, N >= 16384 && K < 16384 ? 4 : 8};
+    if (N < 16384 || K >= 16384) return {1, 2, 16};
+    return K <= 4096 ? KsShape{1, 2, 4} : KsShape{1, 4, 8};
+  }
   auto tiles = [&](int mt, int t) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * t - 1) / (16 * t)); };
   if (M <= 32 && tiles(2, 4) >= 384) return {2, 4, 4};
   if (tiles(4, 4) >= 384) return {4, 4, 4};
@@ -296,7 +313,7 @@ bool gemm_ksplit_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   // whole steps of 128 k inside one group; 32-bit offsets within a tile; the
   // group parameters (or the partial tiles) in LDS
   if (log2g < 7 || K % KS_STEP || 64 * (K / 2) >= (int64_t(1) << 31)) return false;
-  const KsShape c = ks_shape(M, N);
+  const KsShape c = ks_shape(M, N, K);
   const int64_t G = K >> log2g, rows = 16 * c.mt, cols = 16 * c.t;
   return (rows * (G | 1) + G * cols) * 4 <= 160 * 1024 - 1024;
 }
@@ -306,10 +323,18 @@ hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_sca
                                    const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
                                    int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                    int32_t* acc_debug, hipStream_t stream) {
-  const KsShape c = ks_shape(M, N);
+  const KsShape c = ks_shape(M, N, K);
 #define OFFQ_KS(MT, T, P, NB)                                                                     \
   return launch_ks<MT, T, P, NB>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,   \
                                  log2g, y, ldy, acc_debug, stream)
+  if (c.mt == 1) {
+    if (c.t == 4) OFFQ_KS(1, 4, 8, 2);
+    if (c.t == 2 && c.p == 16) OFFQ_KS(1, 2, 16, 2);
+    if (c.t == 2) OFFQ_KS(1, 2, 4, 4);
+    if (c.p == 16) OFFQ_KS(1, 1, 16, 2);
+    if (c.p == 8) OFFQ_KS(1, 1, 8, 4);
+    OFFQ_KS(1, 1, 4, 4);
+  }
   if (c.p == 16) OFFQ_KS(2, 2, 16, 2);
   if (c.t == 1) OFFQ_KS(2, 1, 8, 4);
   if (c.mt == 2) OFFQ_KS(2, 4, 4, 2);

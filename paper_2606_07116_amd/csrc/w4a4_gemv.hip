@@ -18,7 +18,7 @@
 //   same 16 bytes of its token row l % 16 (rows >= M read as zero through the
 //   buffer descriptor), and runs two MFMAs per tile (low and high nibbles, the
 //   same k-permutation on both operands).  Weight nibbles are widened to 16 q.
-//   Steps go in batches of 4; the next batch's loads are issued before the
+//   Steps go in batches of 2; the next batch's loads are issued before the
 //   current batch is multiplied.  One activation load serves T weight loads:
 //   the activation rows are re-read by every row tile, so with T = 1 they
 //   would double the load traffic of M = 16.
@@ -39,21 +39,17 @@ typedef unsigned int p_u32x2 __attribute__((ext_vector_type(2)));
 constexpr int KSTEP = 128;  // k per step (64 packed bytes per row)
 constexpr int GMAX = 256;   // groups whose parameters fit in LDS
 
-// T: 16-channel row tiles per wave (one activation load serves T weight
-// loads); P: waves per workgroup, each taking 1/P of K; BATCH: steps of 128 k
-// per batch of loads (registers).
-template <int T, int P, int BATCH>
-struct GvCfg {
-  static constexpr int THREADS = 64 * P;
-};
+constexpr int T = 2;        // 16-channel row tiles per wave (one activation load serves both)
+constexpr int P = 16;       // waves per workgroup, each taking 1/P of K
+constexpr int BATCH = 2;    // steps of 128 k per batch of loads (registers)
 
-template <int T, int P, int BATCH, bool DBG>
+template <bool DBG>
 __global__ __launch_bounds__(64 * P) void w4a4_gemv_kernel(
     const uint8_t* __restrict__ A, const uint16_t* __restrict__ a_scale,
     const int16_t* __restrict__ a_zero, const uint8_t* __restrict__ W,
     const uint16_t* __restrict__ w_scale, const int32_t* __restrict__ w_colsum, int M, int N,
     int K, int log2g, uint16_t* __restrict__ Y, int64_t ldy, int32_t* __restrict__ acc_dbg) {
-  constexpr int NT = GvCfg<T, P, BATCH>::THREADS;
+  constexpr int NT = 64 * P;
   __shared__ float red[P][64][T * 4];
   // per group: s / 16 and -s z of the 16 token rows, colsum of the tile's channels
   extern __shared__ float gpar[];
@@ -240,62 +236,30 @@ __global__ __launch_bounds__(64 * P) void w4a4_gemv_kernel(
 
 }  // namespace
 
-// Launch shape (T row tiles per wave, K in P parts, BATCH steps per load
-// batch), as measured at M = 16 (g = 128 ... 8192) on the blocked weight
-// layout: wide layers (>= 16384 channels) take two row tiles per wave and K
-// in eighths, batches of two steps (8192 -> 28672: 27.0 -> 25.1 us at
-// M = 16, 27.0 -> 22.8 at M = 1, against four tiles and K in quarters, the
-// best shape of the row-major layout; the same at 4096 -> 28672), or four
-// tiles and K in quarters when K is not a multiple of 2048; narrower ones
-// need more waves in flight:
-// K in eighths with two tiles per wave from 6144 channels, one below, where K
-// splits into eighths of whole batches (from K = 16384 with two tiles: K in
-// sixteenths, batches of two steps: 26.7-27.8 against 29.9-31.4 us at
-// 28672 -> 8192); a K that is a multiple of 2048 but not of 4096 (14336,
-// 6144, 2048) one tile per wave, K in sixteenths and batches of one step
-// (4096 <- 14336 at g = 128: 15.0 -> 11.0 us against quarters in batches of
-// four; 7.9 against 12.3 us at M = 1).  A K that is not a whole number of
-// such batches (short rows, e.g. K = 256) takes one tile per wave, batches
-// of one step and K in as many parts (4, 2, 1) as it divides into.
-static void gemv_shape(int64_t N, int64_t K, int& T, int& P, int& B) {
-  if (N >= 16384) {
-    if (K % 2048 == 0) T = 2, P = 8, B = 2;
-    else T = 4, P = 4, B = 2;
-  } else if (K % 4096 == 0) {
-    T = N >= 6144 ? 2 : 1, P = T == 2 && K >= 16384 ? 16 : 8;
-    B = P == 16 ? 2 : 4;
-  } else if (K % 2048 == 0) {
-    T = 1, P = 16, B = 1;
-  } else {
-    T = 4, P = 4, B = 2;
-  }
-  if (K % ((int64_t)P * KSTEP * B) != 0) {
-    T = 1, B = 1;
-    P = K % (4 * KSTEP) == 0 ? 4 : K % (2 * KSTEP) == 0 ? 2 : 1;
-  }
-}
-
+// Long rows of 6144 to 16383 channels: the group parameters' loads ahead of the
+// stream and the two-batch pipeline are worth more there than the general kernel's
+// freer split (us at M = 16: 28672 -> 8192, g = 512: 23.0 against 25.6, g = 128: 28.6 /
+// 29.6). Everywhere else that one is ahead (16384 -> 16384: 29.4 / 22.6; 8192 -> 10240
+// 21.2 / 15.7; 4096 -> 6144 7.4 / 6.7; 3072 -> 1000, four rows: 8.4 / 4.3).
 bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   // each wave's part of K is a whole number of batches (a part may end inside
   // a group: the group's zero-point term is added once, by the wave holding
   // its first k); no step straddles a group; the group parameters fit in LDS;
   // 32-bit buffer offsets
-  int T, P, B;
-  gemv_shape(N, K, T, P, B);
-  const int64_t batch = (int64_t)P * KSTEP * B;
+  constexpr int64_t batch = (int64_t)P * KSTEP * BATCH;
   // group parameters (dynamic) + the partial sums of the P waves (static)
   const int64_t lds = ((K >> log2g) * (32 + 16 * T) + 16 * T) * 4 + (int64_t)P * 64 * 4 * T * 4;
-  return M <= 16 && log2g >= 7 && K % batch == 0 && (K >> log2g) <= GMAX &&
-         lds <= 160 * 1024 &&
+  return M <= 16 && N >= 6144 && N < 16384 && K >= 16384 && log2g >= 7 && K % batch == 0 &&
+         (K >> log2g) <= GMAX && lds <= 160 * 1024 &&
          32 * (K / 2) < (int64_t(1) << 31) && M * (K / 2) < (int64_t(1) << 31);
 }
 
-template <int T, int P, int BATCH>
-hipError_t launch_gv(const uint8_t* a_codes, const uint16_t* a_scale, const int16_t* a_zero,
-                     const uint8_t* w_codes, const uint16_t* w_scale, const int32_t* w_colsum,
-                     int64_t M, int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
-                     int32_t* acc_debug, hipStream_t stream) {
-  const int rows = 16 * T;
+hipError_t launch_w4a4_gemv_mfma(const uint8_t* a_codes, const uint16_t* a_scale,
+                                 const int16_t* a_zero, const uint8_t* w_codes,
+                                 const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
+                                 int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
+                                 int32_t* acc_debug, hipStream_t stream) {
+  constexpr int rows = 16 * T;
   const dim3 grid((unsigned)((N + rows - 1) / rows)), block(64 * P);
   const size_t lds = ((size_t)(K >> log2g) * (32 + rows) + rows) * sizeof(float);
   // A debug request runs an accumulator-only pass (partial sums added
@@ -304,39 +268,12 @@ hipError_t launch_gv(const uint8_t* a_codes, const uint16_t* a_scale, const int1
     hipError_t e = hipMemsetAsync(acc_debug, 0, (size_t)(K >> log2g) * M * N * sizeof(int32_t),
                                   stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((w4a4_gemv_kernel<T, P, BATCH, true>), grid, block, lds, stream, a_codes,
-                       a_scale, a_zero, w_codes, w_scale, w_colsum, (int)M, (int)N, (int)K, log2g,
-                       y, ldy, acc_debug);
+    hipLaunchKernelGGL((w4a4_gemv_kernel<true>), grid, block, lds, stream, a_codes, a_scale, a_zero,
+                       w_codes, w_scale, w_colsum, (int)M, (int)N, (int)K, log2g, y, ldy, acc_debug);
   }
-  hipLaunchKernelGGL((w4a4_gemv_kernel<T, P, BATCH, false>), grid, block, lds, stream, a_codes, a_scale,
-                     a_zero, w_codes, w_scale, w_colsum, (int)M, (int)N, (int)K, log2g, y, ldy,
-                     acc_debug);
+  hipLaunchKernelGGL((w4a4_gemv_kernel<false>), grid, block, lds, stream, a_codes, a_scale, a_zero,
+                     w_codes, w_scale, w_colsum, (int)M, (int)N, (int)K, log2g, y, ldy, acc_debug);
   return hipGetLastError();
-}
-
-hipError_t launch_w4a4_gemv_mfma(const uint8_t* a_codes, const uint16_t* a_scale,
-                                 const int16_t* a_zero, const uint8_t* w_codes,
-                                 const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
-                                 int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
-                                 int32_t* acc_debug, hipStream_t stream) {
-  int T, P, B;
-  gemv_shape(N, K, T, P, B);
-#define OFFQ_GV(T, P, B)                                                                         \
-  return launch_gv<T, P, B>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g, \
-                            y, ldy, acc_debug, stream)
-  if (B == 1) {
-    if (P == 16) OFFQ_GV(1, 16, 1);
-    if (P == 4) OFFQ_GV(1, 4, 1);
-    if (P == 2) OFFQ_GV(1, 2, 1);
-    OFFQ_GV(1, 1, 1);
-  }
-  if (T == 4) OFFQ_GV(4, 4, 2);
-  if (T == 2 && P == 16) OFFQ_GV(2, 16, 2);
-  if (T == 2 && B == 2) OFFQ_GV(2, 8, 2);
-  if (T == 2) OFFQ_GV(2, 8, 4);
-  if (P == 8) OFFQ_GV(1, 8, 4);
-  OFFQ_GV(1, 4, 4);
-#undef OFFQ_GV
 }
 
 }  // namespace offq

@@ -139,6 +139,19 @@ def test_large_tile_forms(M, N, K, g):
     _layer(M, N, K, g, seed=M + N + K)
 
 
+@pytest.mark.parametrize("M,N,K,g", [
+    (1, 17, 128, 128), (16, 1000, 1792, 256),              # 16 channels by 8 waves; fewer steps than waves
+    (7, 1030, 8320, 128), (2, 6150, 8192, 2048),           # by 16; M <= 4, wide
+    (4, 16390, 640, 128), (3, 16390, 16384, 8192),         # by 4; by 8 on long rows
+    (16, 6150, 4224, 128), (5, 16400, 16512, 128),         # 32 channels by 16; 129 groups
+    (16, 16390, 1024, 512), (9, 16400, 4608, 512),         # 32 by 4, 64 by 8
+    (16, 6150, 16384, 512), (3, 6160, 20480, 128),         # long rows, 160 groups
+])
+def test_decode_shapes(M, N, K, g):
+    """One to sixteen token rows: each split of K and channel tile, ragged."""
+    _layer(M, N, K, g, seed=M + N + K)
+
+
 def test_raw_layout_and_spikes():
     _layer(150, 192, 1024, 1024, seed=5, layout="raw", n_out=6)
 
