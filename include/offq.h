@@ -109,8 +109,8 @@ offq_status_t offq_rotate_quantize(const uint16_t* x, int64_t M, int64_t K, int6
  *
  *   The z * colsum term is the zero-point (offset) correction through
  *   per-column weight sums.  Y is rounded to bf16 (nearest even).  Shapes with
- *   M <= 16 (decode) take a weight-streaming GEMV path; larger M the MFMA
- *   GEMM path.  Results are identical up to fp32 summation order.
+ *   few rows (decode, short prompts) take small tiles that split K, larger ones
+ *   the large-tile kernels.  Results are identical up to fp32 summation order.
  *
  *   a_codes  uint8 [M, K/2] (from offq_rotate_quantize), 16-byte aligned.
  *   a_scale  fp16  [M, K/g];  a_zero int16 [M, K/g].

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void w4a4_gemm_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Decode GEMV (M <= 16) for the shapes the MFMA GEMV does not take (g = 64,
+// Decode GEMV (M <= 16) for the shapes the K-split kernel does not take (g = 64,
 // very many groups): one wavefront per output channel n streams the weight
 // row with 16-byte coalesced loads, lane l taking chunk 64 p + l (32 k) in
 // pass p.  v_dot8_i32_i4 on (q_a - 8, q_w) (activation codes re-biased by

@@ -25,11 +25,11 @@
 //   * 256 x 256 by eight waves of 128 x 64 (FM = 4): two operand bytes expanded per
 //     256 products. At g = 128 the running sums take 128 registers and each
 //     fragment row is folded right after the next row's reads and expansion were
-//     issued. 4096 x 28672 x 4096: 400 -> 313 us with one group (3.07 POP/s),
-//     673 -> 503 us at g = 128, against i8 tiles of 256 x 256 and 256 x 128.
+//     issued. 4096 x 28672 x 4096: 400 -> 304 us with one group (3.16 POP/s),
+//     673 -> 502 us at g = 128, against i8 tiles of 256 x 256 and 256 x 128.
 //   * 128 x 128 by four waves of 64 x 64 (FM = 2), g = 128: two workgroups per CU,
 //     where the larger tiles would not fill whole rounds of the 256 CUs:
-//     1777 x 10240 x 8192 279 -> 219 us (256 x 256: 284).
+//     1777 x 10240 x 8192 279 -> 211 us (256 x 256: 284).
 // Stages go global memory -> registers -> one of two LDS buffers, one LDS-only
 // barrier per stage; loads take whole 64-byte rows.
 #include <type_traits>
@@ -433,7 +433,7 @@ bool f6_large(int64_t M, int64_t N) {
 }  // namespace
 
 bool gemm_fp6_one_group(int64_t M, int64_t N) {
-  // One group per row: a round of 256 x 256 tiles takes 1.39 us a stage, one of the
+  // One group per row: a round of 256 x 256 tiles takes 1.36 us a stage, one of the
   // i8 kernel's 256 x 128 tiles 1.1 us (4096 x 28672 x 4096 and 2048 x 4096 x 4096).
   return 5 * ceil_div(ceil_div(M, 256) * ceil_div(N, 256), 256) <
          4 * ceil_div(ceil_div(M, 256) * ceil_div(N, 128), 256);
