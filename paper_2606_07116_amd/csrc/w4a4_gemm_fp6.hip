@@ -29,7 +29,7 @@
 //     673 -> 502 us at g = 128, against i8 tiles of 256 x 256 and 256 x 128.
 //   * 128 x 128 by four waves of 64 x 64 (FM = 2), g = 128: two workgroups per CU,
 //     where the larger tiles would not fill whole rounds of the 256 CUs:
-//     1777 x 10240 x 8192 279 -> 211 us (256 x 256: 284).
+//     1777 x 10240 x 8192 279 -> 218 us (256 x 256: 284).
 // Stages go global memory -> registers -> one of two LDS buffers, one LDS-only
 // barrier per stage; loads take whole 64-byte rows.
 #include <type_traits>
@@ -127,9 +127,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void w4a4_gemm_fp6_kernel(
   const bool zp_wave = wave >= NWM * NWN / 2;
   const int prow = tid & (BM - 1), pcol = tid & (BN - 1);
   const int rbytes = min(BM, M - tm) * G * 2;
-  // (a column past N reads its neighbour's sum, or 0 past the end: it reaches
-  // only outputs that are not stored)
-  const int cbytes = (int)(((int64_t)G * N - tn) * 4);
+  const int cbytes = min(BN, N - tn) * 4;  // (columns past N read as zero)
   const void* const par0 = !zp_wave ? (const void*)(a_scale + (int64_t)tm * G)
                                   : (const void*)(a_zero + (int64_t)tm * G);
 
@@ -152,8 +150,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void w4a4_gemm_fp6_kernel(
         (void*)par0, 0, last ? rbytes : 0, 0x00020000);
     r.p0 = __builtin_amdgcn_raw_buffer_load_b16(srsrc, prow * G * 2, b * 2, 0);
     const __amdgpu_buffer_rsrc_t crsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(w_colsum + tn), 0, last ? cbytes : 0, 0x00020000);
-    r.pc = (int)__builtin_amdgcn_raw_buffer_load_b32(crsrc, pcol * 4, b * N * 4, 0);
+        (void*)(w_colsum + (int64_t)b * N + tn), 0, last ? cbytes : 0, 0x00020000);
+    r.pc = (int)__builtin_amdgcn_raw_buffer_load_b32(crsrc, pcol * 4, 0, 0);
   };
   char* const sax = ring + sch * OA::XC + srow * 16;
   char* const say = ring + OA::Y + sch * OA::YC + srow * 8;
