@@ -21,8 +21,11 @@ hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
                             uint16_t* y, int64_t ldy, int32_t* acc_debug,
                             hipStream_t stream);
 
-// Any number of groups per row (g >= 256): MFMA GEMM with per-group fold. The size
-// limits hold for the 6-bit kernel too.
+// Sizes that the two large-tile kernels below can address (g >= 128).
+bool gemm_tiles_supported(int64_t M, int64_t N, int64_t K, int log2g);
+
+// Any number of groups per row (g >= 256, refused below): MFMA GEMM with per-group
+// fold.
 bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g);
 hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_scale,
                                     const int16_t* a_zero, const uint8_t* w_codes,

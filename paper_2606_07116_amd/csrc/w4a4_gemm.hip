@@ -309,13 +309,13 @@ hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
   if (few && gemm_ksplit_supported(M, N, K, log2g))
     return launch_w4a4_gemm_ksplit(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
                                    log2g, y, ldy, acc_debug, stream);
-  if (gemm_grouped_supported(M, N, K, log2g)) {
-    if (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N)))
-      return launch_w4a4_gemm_fp6(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
-                                  log2g, y, ldy, acc_debug, stream);
+  if (gemm_tiles_supported(M, N, K, log2g) &&
+      (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N))))
+    return launch_w4a4_gemm_fp6(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
+                                log2g, y, ldy, acc_debug, stream);
+  if (gemm_grouped_supported(M, N, K, log2g))
     return launch_w4a4_gemm_grouped(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N,
                                     K, log2g, y, ldy, acc_debug, stream);
-  }
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const dim3 grid((unsigned)tiles), block(256);
   const bool wide = log2g >= 13;

@@ -635,13 +635,19 @@ __global__ __launch_bounds__(512) void w4a4_gemm_grouped_kernel(
 
 }  // namespace
 
-bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g) {
+bool gemm_tiles_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   // stages of 128 k never straddle a group; buffer offsets (codes, and the
   // streamed group parameters) are 32-bit
   const int64_t G = K >> log2g;
   return log2g >= 7 && K % 128 == 0 && M * (K / 2) < (int64_t(1) << 31) &&
          N * (K / 2) < (int64_t(1) << 31) && G * N * 4 < (int64_t(1) << 31) &&
          256 * G * 2 < (int64_t(1) << 31);
+}
+
+bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g) {
+  // two stages per group at least: the stage loops below have no form for one, and
+  // the one for long groups would never find its last stage
+  return log2g >= 8 && gemm_tiles_supported(M, N, K, log2g);
 }
 
 template <bool ONEG, bool STREAM = false>
@@ -672,6 +678,7 @@ hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_sc
                                     const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
                                     int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                     int32_t* acc_debug, hipStream_t stream) {
+  if (!gemm_grouped_supported(M, N, K, log2g)) return hipErrorInvalidValue;
   if ((K >> log2g) == 1)
     return launch_g<true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
                              y, ldy, acc_debug, stream);

@@ -79,6 +79,28 @@ def test_gemm_validation(args, expect):
     assert st == expect, _lib.last_error()
 
 
+I64, I32, VP = ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p
+
+
+def _internal(mangled, restype, argtypes):
+    """A launcher or rule of csrc/internal.h, by its C++ name."""
+    fn = getattr(ctypes.CDLL(_lib.LIB_PATH), mangled)
+    fn.restype, fn.argtypes = restype, argtypes
+    return fn
+
+
+def test_i8_gemm_refuses_groups_of_one_stage():
+    """The i8 tile kernel has no loop for groups of one stage (g = 128): neither its
+    rule nor its launcher takes them."""
+    rule = _internal("_ZN4offq22gemm_grouped_supportedEllli", ctypes.c_bool, [I64, I64, I64, I32])
+    launch = _internal("_ZN4offq24launch_w4a4_gemm_groupedEPKhPKtPKsS1_S3_PKillliPtlPiP12ihipStream_t",
+                       I32, [VP] * 6 + [I64] * 3 + [I32, VP, I64, VP, VP])
+    assert rule(4096, 4096, 4096, 8) and rule(4096, 4096, 4096, 12)
+    assert not rule(4096, 4096, 4096, 7)
+    hip_error_invalid_value = 1
+    assert launch(P, P, P, P, P, P, 512, 512, 512, 7, P, 512, None, None) == hip_error_invalid_value
+
+
 @pytest.mark.parametrize("args,expect", [
     # (kv, rows, Dh, stride, had, codes, scale, zero, ydbg)
     ((P, 10, 96, 96, 1, P, P, P, None), _lib.OFFQ_ERR_INVALID),
