@@ -14,6 +14,20 @@ hipError_t launch_rotate_quantize(const uint16_t* x, int64_t n_groups, int G,
                                   uint16_t* scale, int16_t* zero, float* y_debug,
                                   int64_t ldy, hipStream_t stream);
 
+// Which kernel a product takes and which form of it; launch_w4a4_gemm goes by it.
+enum GemmKernel : int32_t {
+  kGemmPlain = 0,    // w4a4_gemm.hip: g = 64, K not a multiple of 128, the largest sizes
+  kGemvPlain = 1,    // w4a4_gemm.hip: the same for M <= 16
+  kGemvMfma = 2,     // w4a4_gemv.hip
+  kGemmKsplit = 3,   // w4a4_gemm_ksplit.hip; form: gemm_ksplit_form
+  kGemmGrouped = 4,  // w4a4_gemm_grouped.hip; form: gemm_grouped_form
+  kGemmFp6 = 5,      // w4a4_gemm_fp6.hip; form: gemm_fp6_form
+};
+struct GemmRoute {
+  int32_t kernel, form;
+};
+GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, int log2g);
+
 hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
                             const int16_t* a_zero, const uint8_t* w_codes,
                             const uint16_t* w_scale, const int32_t* w_colsum,
@@ -27,6 +41,8 @@ bool gemm_tiles_supported(int64_t M, int64_t N, int64_t K, int log2g);
 // Any number of groups per row (g >= 256, refused below): MFMA GEMM with per-group
 // fold.
 bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g);
+// 0: one group per row; 1: several, their parameters in LDS; 2: more, streamed
+int gemm_grouped_form(int64_t K, int log2g);
 hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_scale,
                                     const int16_t* a_zero, const uint8_t* w_codes,
                                     const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
@@ -36,6 +52,8 @@ hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_sc
 // One to a few hundred token rows: small output tiles, K split over the waves of a
 // workgroup.
 bool gemm_ksplit_supported(int64_t M, int64_t N, int64_t K, int log2g);
+// 10000 mt + 100 t + p: tiles of 16 mt tokens x 16 t channels by p waves
+int gemm_ksplit_form(int64_t M, int64_t N, int64_t K);
 hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_scale,
                                    const int16_t* a_zero, const uint8_t* w_codes,
                                    const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
@@ -45,6 +63,8 @@ hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_sca
 // The 6-bit matrix format: g = 128, or one group per row on the sizes that
 // gemm_fp6_one_group says it is the faster for.
 bool gemm_fp6_one_group(int64_t M, int64_t N);
+// 0: one group per row, 256 x 256 tiles; 1: g = 128, 256 x 256; 2: g = 128, 128 x 128
+int gemm_fp6_form(int64_t M, int64_t N, int log2g);
 hipError_t launch_w4a4_gemm_fp6(const uint8_t* a_codes, const uint16_t* a_scale,
                                 const int16_t* a_zero, const uint8_t* w_codes,
                                 const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
@@ -58,13 +78,6 @@ hipError_t launch_w4a4_gemv_mfma(const uint8_t* a_codes, const uint16_t* a_scale
                                  const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
                                  int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                  int32_t* acc_debug, hipStream_t stream);
-
-hipError_t launch_w4a4_gemv(const uint8_t* a_codes, const uint16_t* a_scale,
-                            const int16_t* a_zero, const uint8_t* w_codes,
-                            const uint16_t* w_scale, const int32_t* w_colsum,
-                            int64_t M, int64_t N, int64_t K, int log2g,
-                            uint16_t* y, int64_t ldy, int32_t* acc_debug,
-                            hipStream_t stream);
 
 hipError_t launch_pack_weights(const float* w, int64_t N, int64_t K, int log2g,
                                uint8_t* w_codes, uint16_t* w_scale,

@@ -150,19 +150,8 @@ offq_status_t offq_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale, co
       (acc_debug && !aligned(acc_debug, 4)))
     return fail(OFFQ_ERR_INVALID, "misaligned pointer (codes: 16 B)");
   if (offq_status_t s = check_device()) return s;
-  hipError_t e;
-  if (M <= 16 && offq::gemv_mfma_supported(M, N, K, lg))
-    e = offq::launch_w4a4_gemv_mfma(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N,
-                                    K, lg, y, ldy, acc_debug, (hipStream_t)stream);
-  else if (M <= 16 && offq::gemm_ksplit_supported(M, N, K, lg))
-    e = offq::launch_w4a4_gemm_ksplit(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
-                                      lg, y, ldy, acc_debug, (hipStream_t)stream);
-  else if (M <= 16)
-    e = offq::launch_w4a4_gemv(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, lg,
-                               y, ldy, acc_debug, (hipStream_t)stream);
-  else
-    e = offq::launch_w4a4_gemm(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, lg,
-                               y, ldy, acc_debug, (hipStream_t)stream);
+  const hipError_t e = offq::launch_w4a4_gemm(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum,
+                                              M, N, K, lg, y, ldy, acc_debug, (hipStream_t)stream);
   return launched(e, M <= 16 ? "w4a4_gemv" : "w4a4_gemm");
 }
 

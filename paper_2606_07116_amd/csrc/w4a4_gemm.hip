@@ -287,35 +287,10 @@ __global__ __launch_bounds__(256) void w4a4_gemv_kernel(
   }
 }
 
-}  // namespace
-
-hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
-                            const int16_t* a_zero, const uint8_t* w_codes,
-                            const uint16_t* w_scale, const int32_t* w_colsum,
-                            int64_t M, int64_t N, int64_t K, int log2g,
-                            uint16_t* y, int64_t ldy, int32_t* acc_debug,
-                            hipStream_t stream) {
-  // Few rows leave the grid of large tiles short of the 256 CUs, or the tiles
-  // mostly padding: small tiles with K split inside the workgroup instead.
-  // At g = 128 up to 512 tiles of 64 x 64 (333 x 4096 x 14336, 384 tiles: 62 us, by
-  // 128 x 128 tiles 102; 2000 x 1000 x 8192, 512 tiles: 42 / 62; but 333 x 6144 x
-  // 4096, 576 tiles: 37 / 35, and 700 x 4096 x 14336, 704 tiles: 121 / 104). Longer
-  // groups fold less and their large tiles cost less: up to 128 of 256 x 128 (700 x
-  // 4096 x 14336, g = 512: 85 / 104; 500 x 10240 x 8192 one group: 78 / 57), twice
-  // that where half a tile's rows are padding.
-  const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
-  const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
-  const bool few = log2g == 7 ? tiles64 <= 512 : tiles256 <= (M <= 128 ? 256 : 128);
-  if (few && gemm_ksplit_supported(M, N, K, log2g))
-    return launch_w4a4_gemm_ksplit(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
-                                   log2g, y, ldy, acc_debug, stream);
-  if (gemm_tiles_supported(M, N, K, log2g) &&
-      (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N))))
-    return launch_w4a4_gemm_fp6(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
-                                log2g, y, ldy, acc_debug, stream);
-  if (gemm_grouped_supported(M, N, K, log2g))
-    return launch_w4a4_gemm_grouped(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N,
-                                    K, log2g, y, ldy, acc_debug, stream);
+hipError_t launch_gemm_plain(const uint8_t* a_codes, const uint16_t* a_scale, const int16_t* a_zero,
+                             const uint8_t* w_codes, const uint16_t* w_scale,
+                             const int32_t* w_colsum, int64_t M, int64_t N, int64_t K, int log2g,
+                             uint16_t* y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
   const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const dim3 grid((unsigned)tiles), block(256);
   const bool wide = log2g >= 13;
@@ -332,12 +307,10 @@ hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
   return hipGetLastError();
 }
 
-hipError_t launch_w4a4_gemv(const uint8_t* a_codes, const uint16_t* a_scale,
-                            const int16_t* a_zero, const uint8_t* w_codes,
-                            const uint16_t* w_scale, const int32_t* w_colsum,
-                            int64_t M, int64_t N, int64_t K, int log2g,
-                            uint16_t* y, int64_t ldy, int32_t* acc_debug,
-                            hipStream_t stream) {
+hipError_t launch_gemv_plain(const uint8_t* a_codes, const uint16_t* a_scale, const int16_t* a_zero,
+                             const uint8_t* w_codes, const uint16_t* w_scale,
+                             const int32_t* w_colsum, int64_t M, int64_t N, int64_t K, int log2g,
+                             uint16_t* y, int64_t ldy, int32_t* acc_debug, hipStream_t stream) {
   const dim3 grid((unsigned)((N + 3) / 4)), block(256);
 #define OFFQ_GEMV(MT, D)                                                                  \
   hipLaunchKernelGGL((w4a4_gemv_kernel<MT, D>), grid, block, 0, stream, a_codes, a_scale, \
@@ -352,6 +325,54 @@ hipError_t launch_w4a4_gemv(const uint8_t* a_codes, const uint16_t* a_scale,
   }
 #undef OFFQ_GEMV
   return hipGetLastError();
+}
+
+}  // namespace
+
+GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, int log2g) {
+  const GemmRoute ksplit = {kGemmKsplit, gemm_ksplit_form(M, N, K)};
+  if (M <= 16) {
+    if (gemv_mfma_supported(M, N, K, log2g)) return {kGemvMfma, 0};
+    if (gemm_ksplit_supported(M, N, K, log2g)) return ksplit;
+    return {kGemvPlain, 0};
+  }
+  // Few rows leave the grid of large tiles short of the 256 CUs, or the tiles
+  // mostly padding: small tiles with K split inside the workgroup instead.
+  // At g = 128 up to 512 tiles of 64 x 64 (333 x 4096 x 14336, 384 tiles: 62 us, by
+  // 128 x 128 tiles 102; 2000 x 1000 x 8192, 512 tiles: 42 / 62; but 333 x 6144 x
+  // 4096, 576 tiles: 37 / 35, and 700 x 4096 x 14336, 704 tiles: 121 / 104). Longer
+  // groups fold less and their large tiles cost less: up to 128 of 256 x 128 (700 x
+  // 4096 x 14336, g = 512: 85 / 104; 500 x 10240 x 8192 one group: 78 / 57), twice
+  // that where half a tile's rows are padding.
+  const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
+  const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
+  const bool few = log2g == 7 ? tiles64 <= 512 : tiles256 <= (M <= 128 ? 256 : 128);
+  if (few && gemm_ksplit_supported(M, N, K, log2g)) return ksplit;
+  if (gemm_tiles_supported(M, N, K, log2g) &&
+      (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N))))
+    return {kGemmFp6, gemm_fp6_form(M, N, log2g)};
+  if (gemm_grouped_supported(M, N, K, log2g)) return {kGemmGrouped, gemm_grouped_form(K, log2g)};
+  return {kGemmPlain, 0};
+}
+
+hipError_t launch_w4a4_gemm(const uint8_t* a_codes, const uint16_t* a_scale,
+                            const int16_t* a_zero, const uint8_t* w_codes,
+                            const uint16_t* w_scale, const int32_t* w_colsum,
+                            int64_t M, int64_t N, int64_t K, int log2g,
+                            uint16_t* y, int64_t ldy, int32_t* acc_debug,
+                            hipStream_t stream) {
+#define OFFQ_GO(F)                                                                          \
+  return F(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g, y, ldy, \
+           acc_debug, stream)
+  switch (gemm_route(M, N, K, log2g).kernel) {
+    case kGemvMfma: OFFQ_GO(launch_w4a4_gemv_mfma);
+    case kGemmKsplit: OFFQ_GO(launch_w4a4_gemm_ksplit);
+    case kGemmGrouped: OFFQ_GO(launch_w4a4_gemm_grouped);
+    case kGemmFp6: OFFQ_GO(launch_w4a4_gemm_fp6);
+    case kGemvPlain: OFFQ_GO(launch_gemv_plain);
+    default: OFFQ_GO(launch_gemm_plain);
+  }
+#undef OFFQ_GO
 }
 
 }  // namespace offq

@@ -437,6 +437,10 @@ bool gemm_fp6_one_group(int64_t M, int64_t N) {
          4 * ceil_div(ceil_div(M, 256) * ceil_div(N, 128), 256);
 }
 
+int gemm_fp6_form(int64_t M, int64_t N, int log2g) {
+  return log2g != 7 ? 0 : f6_large(M, N) ? 1 : 2;
+}
+
 hipError_t launch_w4a4_gemm_fp6(const uint8_t* a_codes, const uint16_t* a_scale,
                                 const int16_t* a_zero, const uint8_t* w_codes,
                                 const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
@@ -445,9 +449,11 @@ hipError_t launch_w4a4_gemm_fp6(const uint8_t* a_codes, const uint16_t* a_scale,
 #define OFFQ_F6_GO(FM, NWM, NWN, FOLD)                                                       \
   return launch_f6<FM, NWM, NWN, FOLD>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, \
                                        M, N, K, log2g, y, ldy, acc_debug, stream)
-  if (log2g != 7) OFFQ_F6_GO(4, 2, 4, 0);
-  if (f6_large(M, N)) OFFQ_F6_GO(4, 2, 4, 1);
-  OFFQ_F6_GO(2, 2, 2, 1);
+  switch (gemm_fp6_form(M, N, log2g)) {
+    case 0: OFFQ_F6_GO(4, 2, 4, 0);
+    case 1: OFFQ_F6_GO(4, 2, 4, 1);
+    default: OFFQ_F6_GO(2, 2, 2, 1);
+  }
 #undef OFFQ_F6_GO
 }
 

@@ -650,6 +650,13 @@ bool gemm_grouped_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   return log2g >= 8 && gemm_tiles_supported(M, N, K, log2g);
 }
 
+int gemm_grouped_form(int64_t K, int log2g) {
+  // several groups: the parameters of up to 28 groups sit in LDS for the whole
+  // tile; more groups stream theirs with the stages
+  const int64_t G = K >> log2g;
+  return G == 1 ? 0 : G <= GCfg<false>::GMAX ? 1 : 2;
+}
+
 template <bool ONEG, bool STREAM = false>
 hipError_t launch_g(const uint8_t* a_codes, const uint16_t* a_scale, const int16_t* a_zero,
                     const uint8_t* w_codes, const uint16_t* w_scale, const int32_t* w_colsum,
@@ -679,16 +686,15 @@ hipError_t launch_w4a4_gemm_grouped(const uint8_t* a_codes, const uint16_t* a_sc
                                     int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                     int32_t* acc_debug, hipStream_t stream) {
   if (!gemm_grouped_supported(M, N, K, log2g)) return hipErrorInvalidValue;
-  if ((K >> log2g) == 1)
-    return launch_g<true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
-                             y, ldy, acc_debug, stream);
-  // several groups: the parameters of up to 28 groups sit in LDS for the whole
-  // tile; more groups stream theirs with the stages
-  if ((K >> log2g) > GCfg<false>::GMAX)
-    return launch_g<false, true>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,
-                                    log2g, y, ldy, acc_debug, stream);
-  return launch_g<false>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, log2g,
-                            y, ldy, acc_debug, stream);
+#define OFFQ_G_GO(...)                                                                        \
+  return launch_g<__VA_ARGS__>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, \
+                               log2g, y, ldy, acc_debug, stream)
+  switch (gemm_grouped_form(K, log2g)) {
+    case 0: OFFQ_G_GO(true);
+    case 1: OFFQ_G_GO(false);
+    default: OFFQ_G_GO(false, true);
+  }
+#undef OFFQ_G_GO
 }
 
 }  // namespace offq

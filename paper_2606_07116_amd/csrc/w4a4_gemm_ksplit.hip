@@ -318,30 +318,36 @@ bool gemm_ksplit_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   return (rows * (G | 1) + G * cols) * 4 <= 160 * 1024 - 1024;
 }
 
+int gemm_ksplit_form(int64_t M, int64_t N, int64_t K) {
+  const KsShape c = ks_shape(M, N, K);
+  return 10000 * c.mt + 100 * c.t + c.p;
+}
+
 hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_scale,
                                    const int16_t* a_zero, const uint8_t* w_codes,
                                    const uint16_t* w_scale, const int32_t* w_colsum, int64_t M,
                                    int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                    int32_t* acc_debug, hipStream_t stream) {
-  const KsShape c = ks_shape(M, N, K);
-#define OFFQ_KS(MT, T, P, NB)                                                                     \
-  return launch_ks<MT, T, P, NB>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K,   \
-                                 log2g, y, ldy, acc_debug, stream)
-  if (c.mt == 1) {
-    if (c.t == 4) OFFQ_KS(1, 4, 8, 2);
-    if (c.t == 2 && c.p == 16) OFFQ_KS(1, 2, 16, 2);
-    if (c.t == 2) OFFQ_KS(1, 2, 4, 4);
-    if (c.p == 16) OFFQ_KS(1, 1, 16, 2);
-    if (c.p == 8) OFFQ_KS(1, 1, 8, 4);
+#define OFFQ_KS(MT, T, P, NB)                                                                   \
+  case 10000 * MT + 100 * T + P:                                                                \
+    return launch_ks<MT, T, P, NB>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, \
+                                   log2g, y, ldy, acc_debug, stream)
+  switch (gemm_ksplit_form(M, N, K)) {
     OFFQ_KS(1, 1, 4, 4);
+    OFFQ_KS(1, 1, 8, 4);
+    OFFQ_KS(1, 1, 16, 2);
+    OFFQ_KS(1, 2, 4, 4);
+    OFFQ_KS(1, 2, 16, 2);
+    OFFQ_KS(1, 4, 8, 2);
+    OFFQ_KS(2, 1, 8, 4);
+    OFFQ_KS(2, 2, 16, 2);
+    OFFQ_KS(2, 4, 4, 2);
+    OFFQ_KS(4, 2, 8, 1);
+    OFFQ_KS(4, 4, 4, 1);
+    OFFQ_KS(4, 4, 8, 1);
   }
-  if (c.p == 16) OFFQ_KS(2, 2, 16, 2);
-  if (c.t == 1) OFFQ_KS(2, 1, 8, 4);
-  if (c.mt == 2) OFFQ_KS(2, 4, 4, 2);
-  if (c.t == 2) OFFQ_KS(4, 2, 8, 1);
-  if (c.p == 4) OFFQ_KS(4, 4, 4, 1);
-  OFFQ_KS(4, 4, 8, 1);
 #undef OFFQ_KS
+  return hipErrorInvalidValue;
 }
 
 }  // namespace offq
