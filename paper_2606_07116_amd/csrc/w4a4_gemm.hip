@@ -329,6 +329,26 @@ hipError_t launch_gemv_plain(const uint8_t* a_codes, const uint16_t* a_scale, co
 
 }  // namespace
 
+// Up to how many tiles of 64 x 64 the K-split kernel is the faster for. Its time grows
+// with them, that of one round of large tiles does not, so the line lies where the two
+// meet (us, K-split / large tiles, N = 4096):
+//   g = 128 (M x N x K): 512 x 4096 x 4096, 512 tiles, 24 / 33, 512 x 4096 x 14336
+//     73 / 102; 333 x 6144 x 4096, 576 tiles, 38 / 34, 333 x 6144 x 14336 111 / 103;
+//   short K: 768 x 4096 x 1024, 768 tiles, one group 15.1 / 12.4;
+//   one group or groups of 1024 and more: 640 rows at K = 8192, 640 tiles, 43 / 51;
+//     768 at K = 4096, 768 tiles, 31 / 29, 1024, 1024 tiles, 34 / 29;
+//   groups of 512, which cost the large tiles more folds: 768 rows at K = 14336,
+//     768 tiles, 88 / 101; 850 at K = 4096, 896 tiles, 33.9 / 33.2;
+//   groups of 256, and more groups than the large tiles keep in LDS, most of all: 1024
+//     rows, 1024 tiles: K = 14336, g = 256, 115 / 131; K = 28672, g = 512, 192 / 233;
+//     1000 x 6144 x 4096, g = 256, 1536 tiles, 50 / 47.
+static int64_t ksplit_tiles(int64_t K, int log2g) {
+  if (log2g == 7 || K < 2048) return 512;
+  if (log2g == 8 || gemm_grouped_form(K, log2g) == 2) return 1024;
+  if (K < 4096) return 512;
+  return log2g == 9 ? 768 : 640;
+}
+
 GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, int log2g) {
   const GemmRoute ksplit = {kGemmKsplit, gemm_ksplit_form(M, N, K)};
   if (M <= 16) {
@@ -338,15 +358,8 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, int log2g) {
   }
   // Few rows leave the grid of large tiles short of the 256 CUs, or the tiles
   // mostly padding: small tiles with K split inside the workgroup instead.
-  // At g = 128 up to 512 tiles of 64 x 64 (333 x 4096 x 14336, 384 tiles: 62 us, by
-  // 128 x 128 tiles 102; 2000 x 1000 x 8192, 512 tiles: 42 / 62; but 333 x 6144 x
-  // 4096, 576 tiles: 37 / 35, and 700 x 4096 x 14336, 704 tiles: 121 / 104). Longer
-  // groups fold less and their large tiles cost less: up to 128 of 256 x 128 (700 x
-  // 4096 x 14336, g = 512: 85 / 104; 500 x 10240 x 8192 one group: 78 / 57), twice
-  // that where half a tile's rows are padding.
   const int64_t tiles64 = ((M + 63) / 64) * ((N + 63) / 64);
-  const int64_t tiles256 = ((M + 255) / 256) * ((N + 127) / 128);
-  const bool few = log2g == 7 ? tiles64 <= 512 : tiles256 <= (M <= 128 ? 256 : 128);
+  const bool few = tiles64 <= ksplit_tiles(K, log2g);
   if (few && gemm_ksplit_supported(M, N, K, log2g)) return ksplit;
   if (gemm_tiles_supported(M, N, K, log2g) &&
       (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N))))
