@@ -1,9 +1,11 @@
-"""Host-only checks of the product dispatch: which kernel and form a call takes."""
+"""Host-only checks of the product dispatch: which kernel and form a call takes, and
+that the GPU tests run every form that some call takes."""
 import ctypes
 
 import pytest
 
 from paper_2606_07116_amd import _lib
+from tests import test_gpu_gemm as G
 
 I64, I32 = ctypes.c_int64, ctypes.c_int32
 KERNELS = ("plain", "plain_gemv", "gemv", "ksplit", "i8", "fp6")
@@ -50,3 +52,43 @@ def test_routes(size, expect):
 ])
 def test_ksplit_ends_where_large_tiles_are_faster(M, N, K, g, kernel):
     assert route(M, N, K, g)[0] == kernel
+
+
+def _tested():
+    shapes = [(5, 200, 1024, 64)]  # (of test_gemv_shapes)
+    for t in (G.test_gemm_shapes, G.test_large_gemm_shapes, G.test_gemv_parts_of_k,
+              G.test_few_token_rows, G.test_large_tile_forms, G.test_decode_shapes):
+        shapes += next(m for m in t.pytestmark if m.name == "parametrize").args[1]
+    return shapes
+
+
+def _reachable():
+    """Every route over a grid of sizes."""
+    out = {}
+    for K in (128, 256, 384, 640, 1024, 1536, 2048, 4096, 6144, 8192, 11008, 14336, 16384, 20480,
+              28672, 32768):
+        for g in (64, 128, 256, 512, 1024, 2048, 4096, 8192):
+            if K % g:
+                continue
+            for N in (64, 1000, 4096, 5120, 8192, 10240, 14336, 16384, 28672, 57344):
+                for M in (1, 4, 5, 16, 17, 33, 64, 100, 333, 600, 1000, 2048, 4096, 16384):
+                    out.setdefault(route(M, N, K, g), (M, N, K, g))
+    return out
+
+
+def test_gpu_tests_run_every_form_that_a_call_takes():
+    """Each form is run at least once, and once at sizes that leave remainders in both
+    the rows and the columns."""
+    tested = {route(*s) for s in _tested()}
+    ragged = {route(*s) for s in _tested() if s[0] % 16 and s[1] % 16}
+    reach = _reachable()
+    assert len(reach) > 20
+    missing = {r: s for r, s in reach.items() if r not in tested}
+    assert not missing, missing
+    assert not {r: s for r, s in reach.items() if r not in ragged}
+
+
+def test_large_tile_list_has_every_form():
+    """The shapes that the output-stride and extreme-value tests run."""
+    assert [route(*s) for s in G.LARGE_TILES] == [("fp6", 2), ("fp6", 1), ("fp6", 0), ("i8", 0, 4),
+                                                  ("i8", 1, 4), ("i8", 2, 2)]

@@ -34,11 +34,9 @@ def _layer(M, N, K, g, seed, layout="concentrated", n_out=4):
 @pytest.mark.parametrize("M,N,K,g", [
     (17, 8, 256, 256), (128, 128, 512, 512), (130, 136, 1024, 256), (200, 250, 256, 64),
     (257, 384, 2048, 512), (64, 512, 4096, 4096), (40, 96, 8192, 8192), (33, 64, 512, 128),
-    # groups of 8 and 16 stages of 128 k; more groups than the grouped kernel
-    # keeps in LDS (G = 32); g = 512 over a ragged 2-tile-row x 3-tile-column grid
+    # groups of 8 and 16 steps of 128 k; 32 groups; g = 512 over a ragged grid
     (100, 136, 4096, 1024), (77, 64, 8192, 2048), (40, 64, 4096, 128), (300, 260, 3584, 512),
-    # more groups than fit in LDS (parameters streamed with the stages): one,
-    # two, four and sixteen stages per group, an odd number of groups
+    # many groups: of one, two, four and sixteen steps, an odd number of them
     (257, 200, 14336, 128), (300, 136, 8192, 256), (100, 520, 16384, 512),
     (33, 130, 3712, 128), (64, 96, 65536, 2048),
 ])
@@ -48,10 +46,9 @@ def test_gemm_shapes(M, N, K, g):
 
 @pytest.mark.parametrize("M,N,K", [(4096, 6144, 4096), (4000, 6100, 1024)])
 def test_wide_tile_gemm_accumulators(M, N, K):
-    """One group per row on at least 384 tiles of 256 x 256: the wide-tile
-    kernel that the MLP up/gate projection and the 8192-row projection run.
-    Every accumulator bit-exact, once on whole tiles and once ragged in M and
-    N (384 tiles again)."""
+    """One group per row on 384 tiles of 256 x 256: the form that the MLP up/gate
+    projection and the 8192-row projection run. Every accumulator bit-exact, once on
+    whole tiles and once ragged in M and N."""
     _layer(M, N, K, K, seed=M + N)
 
 
@@ -130,8 +127,13 @@ def test_few_token_rows(M, N, K, g):
     (1030, 4098, 640, 128), (513, 8200, 4096, 128),
     (4096, 4096, 256, 128), (4001, 4090, 640, 128),        # g = 128, 256 x 256 tiles
     (4000, 4000, 1024, 1024), (3841, 4090, 512, 512),      # one group, 256 x 256 tiles
-    (2040, 4090, 512, 512), (1800, 5000, 2048, 2048),      # one group, 256 x 128 tiles
+    (1800, 5000, 2048, 2048), (2100, 3722, 8192, 8192),    # ... long: the largest sums
+    (2040, 4090, 512, 512), (2040, 4090, 256, 256),        # one group, 256 x 128 tiles on i8
+    (2039, 4090, 2048, 2048),
+    (2001, 2090, 1280, 256), (1990, 2100, 1536, 512),      # 5, 3 groups in LDS
+    (1990, 2100, 3072, 1024),
     (1500, 6150, 8192, 256), (1300, 6200, 7936, 256),      # 32 and 31 groups of 256, streamed
+    (2051, 2053, 14848, 512), (2049, 2058, 29696, 1024),   # 29 groups of 512, of 1024, streamed
 ])
 def test_large_tile_forms(M, N, K, g):
     """Each large-tile kernel at ragged edges, with the smallest and odd stage
@@ -146,6 +148,8 @@ def test_large_tile_forms(M, N, K, g):
     (16, 6150, 4224, 128), (5, 16400, 16512, 128),         # 32 channels by 16; 129 groups
     (16, 16390, 1024, 512), (9, 16400, 4608, 512),         # 32 by 4, 64 by 8
     (16, 6150, 16384, 512), (3, 6160, 20480, 128),         # long rows, 160 groups
+    (5, 6150, 16384, 2048),
+    (7, 6150, 4224, 128), (5, 16390, 4096, 1024), (9, 16390, 4608, 512),
 ])
 def test_decode_shapes(M, N, K, g):
     """One to sixteen token rows: each split of K and channel tile, ragged."""
@@ -194,6 +198,80 @@ def test_extreme_codes_and_zero_points():
     acc_ref = OG.int_gemm_groups(np.full((M, K), 15, np.uint8), q_w, g)
     assert np.array_equal(P.host(acc), acc_ref)
     P.check_output(P.host(y.float()), acc_ref, P.host(scale), P.host(zero), sw, cs)
+
+
+# one shape for each large-tile form: 6-bit 128 x 128 and 256 x 256 at g = 128 and with
+# one group, i8 with one group, groups in LDS and streamed; M and N leave remainders
+LARGE_TILES = [(645, 6150, 256, 128), (4001, 4090, 256, 128), (3841, 4090, 512, 512),
+               (2040, 4090, 512, 512), (1990, 2100, 1024, 512), (2049, 2053, 7424, 256)]
+
+
+def _random_product(M, N, K, g, z):
+    """Random codes of both operands with the zero-points z: GPU operands and the
+    oracle's accumulators, scales and column sums."""
+    rng = np.random.default_rng(M + N)
+    q = rng.integers(0, 16, (M, K), dtype=np.uint8)
+    q_w = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    s = rng.uniform(0.05, 0.5, (M, K // g)).astype(np.float16)
+    sw = rng.uniform(0.01, 0.1, N).astype(np.float16)
+    cs = OQ.colsum(q_w, g)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(P.DEV)
+    ops = (up(OQ.pack_nibbles(q)), up(s), up(z)) + P.upload_weights(OQ.pack_nibbles(q_w), sw, cs)
+    return ops, (OG.int_gemm_groups(q, q_w, g), s, z, sw, cs)
+
+
+@pytest.mark.parametrize("M,N,K,g", LARGE_TILES)
+def test_large_tile_output_row_stride(M, N, K, g):
+    """A strided output view off 16-byte boundaries, whole tiles and ragged ones:
+    nothing around it is written, and its values are those of a dense output."""
+    z = np.random.default_rng(1).integers(-40, 40, (M, K // g)).astype(np.int16)
+    ops, _ = _random_product(M, N, K, g, z)
+    dense, _ = offq.offq_w4a4_gemm(*ops, g)
+    for ld, off in ((N + 29, 3), (N + 6, 0)):
+        big = torch.full((M, ld), 7.0, dtype=torch.bfloat16, device=P.DEV)
+        offq.offq_w4a4_gemm(*ops, g, out=big[:, off:off + N])
+        torch.cuda.synchronize()
+        assert torch.equal(big[:, off:off + N], dense)
+        assert bool((big[:, :off] == 7.0).all()) and bool((big[:, off + N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K,g", LARGE_TILES + [(2100, 3722, 8192, 8192), (333, 1000, 2048, 128),
+                                                   (9, 1000, 2048, 128), (9, 6150, 16384, 512)])
+def test_large_zero_points(M, N, K, g):
+    """Zero-points over the whole int16 range and at both its ends: |z colsum| up to
+    2^25 in a group of 128 and far beyond with one group, so that a group's term and
+    its products no longer fit 24 bits together. The bar of the other tests holds (with
+    one group: a bf16 neighbour of the exact value)."""
+    z = np.random.default_rng(2).integers(-32768, 32768, (M, K // g)).astype(np.int16)
+    z[::3] = 32767
+    z[1::3] = -32768
+    ops, ref = _random_product(M, N, K, g, z)
+    y, acc = offq.offq_w4a4_gemm(*ops, g, debug=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(P.host(acc), ref[0])
+    P.check_output(P.host(y.float()), *ref)
+
+
+@pytest.mark.parametrize("M,N,K,g", LARGE_TILES + [(2100, 3722, 8192, 8192)])
+def test_largest_sums(M, N, K, g):
+    """All-15 activation codes against all -8 weights: the largest accumulators and
+    column sums of every large-tile form, with the largest zero-points."""
+    q = np.full((M, K), 15, np.uint8)
+    q_w = np.full((N, K), -8, np.int8)
+    z = np.where(np.arange(M) % 2, 32767, -32768).astype(np.int16)[:, None].repeat(K // g, 1)
+    s = np.full((M, K // g), 0.5, np.float16)
+    sw = np.full(N, 0.25, np.float16)
+    cs = OQ.colsum(q_w, g)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(P.DEV)
+    y, acc = offq.offq_w4a4_gemm(up(OQ.pack_nibbles(q)), up(s), up(z),
+                                 *P.upload_weights(OQ.pack_nibbles(q_w), sw, cs), g, debug=True)
+    torch.cuda.synchronize()
+    # every row and column alike: one column's sums stand for all
+    acc_ref = OG.int_gemm_groups(q[:2], q_w[:2], g)
+    assert np.all(P.host(acc) == acc_ref[0, 0, 0])
+    y_ref = OG.epilogue(np.broadcast_to(acc_ref[:, :1, :1], (K // g, M, 2)), s, z, sw[:2], cs[:, :2])
+    y = P.host(y.float()).astype(np.float64)
+    assert np.all(np.abs(y - y_ref[:, :1]) <= OG.bf16_ulp(y_ref[:, :1]))
 
 
 def test_empty_m_is_noop():
