@@ -275,7 +275,10 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 // eight waves or 384 of four; larger tiles reload less, more parts of K fill
 // the chip where the output is small:
 //   64 x 64 tiles by 4 waves from 384 tiles (64 x 28672 x 4096: 27.0, by 8 waves 32.0;
-//     512 x 4096 x 4096: 19.4 / 24.7), 32 x 64 tiles where M <= 32;
+//     512 x 4096 x 4096: 19.4 / 24.7), 32 x 64 tiles where M <= 32; from 192 where a
+//     wave of eight has one step of K or none (1280 x 1024 x 1024: 9.0, by 8 waves 13.1;
+//     1280 x 1024 x 512: 7.7 / 11.7; 17 x 14336 x 256, 32 x 64 tiles, 4.8, 64 x 32 by 8
+//     waves 8.1);
 //   by 8 waves from 256 tiles (1000 x 1000 x 8192: 20.0, by 4 waves 24.5);
 //   32 x 32 tiles by 16 waves up to 256 of them (64 x 4096 x 14336: 19.3; 64 x 32 by
 //     8 waves 31), 32 x 16 by 8 waves up to 64 (17 x 1024 x 4096: 6.4 / 7.3);
@@ -299,8 +302,9 @@ KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
     return K <= 4096 ? KsShape{1, 2, 4} : KsShape{1, 4, 8};
   }
   auto tiles = [&](int mt, int t) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * t - 1) / (16 * t)); };
-  if (M <= 32 && tiles(2, 4) >= 384) return {2, 4, 4};
-  if (tiles(4, 4) >= 384) return {4, 4, 4};
+  const int four = K <= 1024 ? 192 : 384;
+  if (M <= 32 && tiles(2, 4) >= four) return {2, 4, 4};
+  if (tiles(4, 4) >= four) return {4, 4, 4};
   if (M > 32 && tiles(4, 4) >= 256) return {4, 4, 8};
   if (tiles(2, 2) <= 64) return {2, 1, 8};
   if (tiles(2, 2) <= 256) return {2, 2, 16};

@@ -54,6 +54,15 @@ def test_ksplit_ends_where_large_tiles_are_faster(M, N, K, g, kernel):
     assert route(M, N, K, g)[0] == kernel
 
 
+@pytest.mark.parametrize("M,N,K,g,form", [
+    # short K: the sums of eight or sixteen waves took longer than their one step
+    (1280, 1024, 512, 512, 40404), (1280, 1024, 1024, 1024, 40404), (96, 10240, 512, 512, 40404),
+    (17, 14336, 256, 256, 20404), (1280, 1024, 2048, 2048, 40408),
+])
+def test_ksplit_forms(M, N, K, g, form):
+    assert route(M, N, K, g) == ("ksplit", form)
+
+
 def _tested():
     shapes = [(5, 200, 1024, 64)]  # (of test_gemv_shapes)
     for t in (G.test_gemm_shapes, G.test_large_gemm_shapes, G.test_gemv_parts_of_k,

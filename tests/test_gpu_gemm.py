@@ -112,7 +112,8 @@ def test_gemv_parts_of_k(M, N, K, g):
     (33, 4096, 640, 128), (64, 2040, 14336, 128),          # 32 x 32, fewer steps than waves; 112 groups
     (64, 6150, 512, 256), (65, 4100, 3072, 1024),          # 64 x 32; parts of K that end inside a group
     (32, 24580, 384, 128), (20, 24600, 1024, 1024),        # 32 x 64
-    (250, 4100, 896, 128), (100, 8200, 2048, 2048),        # 64 x 64 by eight waves
+    (250, 4100, 1152, 128), (100, 8200, 2048, 2048),       # 64 x 64 by eight waves
+    (250, 4100, 896, 128), (1270, 1030, 128, 128),         # ... by four: short K
     (333, 4096, 1536, 512), (257, 6145, 768, 256),         # 64 x 64 by four waves
 ])
 def test_few_token_rows(M, N, K, g):
