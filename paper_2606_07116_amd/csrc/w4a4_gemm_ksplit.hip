@@ -285,21 +285,41 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //   64 x 32 tiles by 8 waves between (64 x 6144 x 4096: 12.5; 32 x 32 tiles 14.1).
 // Up to 16 rows the weights' stream bounds it, and waves in flight (per byte) carry
 // it; the activations are read again by every channel tile, which counts from about
-// five rows:
-//   narrow outputs 16 channels by 8 waves, by 16 from K = 8192 (16 x 4096 x 4096: 5.2;
-//     1 x 4096 x 14336: 9.2, by 8 waves 10.5);
-//   wider ones with M <= 4 the same by 8 waves, by 4 from N = 16384 (1 x 10240 x 8192:
-//     11.4; 1 x 28672 x 4096: 13.5, by 8 waves 15.1);
+// five rows. Sweeps over M = 1 ... 16, N = 64 ... 57344, K = 128 ... 32768:
+//   a wave per two to four steps of a short K: more of them only add to the reduction
+//     (8 x 10240 x 128 2.8, by 16 waves 4.7; 5 x 10240 x 512 3.9 / 5.1; 1 x 14336 x 768
+//     4.3, by 8 waves 5.0);
+//   narrow outputs 16 channels by 8 waves, by 16 from K = 5120 (16 x 4096 x 4096: 5.2;
+//     1 x 4096 x 14336: 9.2, by 8 waves 10.5; 1 x 1000 x 6144 4.6 / 5.1);
+//   wider ones with M <= 4 the same by 8 waves, below 10240 channels by 16 where that
+//     leaves whole batches (1 x 5120 x 6144 7.4 / 7.8), and by 4 from N = 16384 up to
+//     K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves 15.0; 1 x 16384 x 8192 18.5 / 15.4);
 //   with more rows 32 channels by 16 waves (16 x 14336 x 4096: 10.2; 16 channels by 8
-//     waves 11.5), from N = 16384 by 4 waves where K is short (16 x 28672 x 4096: 16.3 /
-//     16.8), 64 channels by 8 where it is longer (16 x 28672 x 8192: 23.5 / 24.3).
+//     waves 11.5), by 8 below K = 4096 and from 6144 to 10240, where 16 have too few
+//     steps (16 x 8192 x 8192 10.2 / 10.9; from N = 10240 16 channels: 5 x 10240 x 1536
+//     4.9 / 5.9);
+//   from N = 16384 by 8 waves (5 x 20480 x 8192 17.7, 64 channels by 8 20.5), by 4 at
+//     K = 4096 (16 x 28672 x 4096: 16.6 / 17.4), 64 channels by 8 where rows and
+//     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K = 16384 on
+//     except at its multiples, whose sixteenths are a power of two apart (16 x 20480 x
+//     28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2).
 struct KsShape { int mt, t, p; };
 KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
   if (M <= 16) {
-    if (N < 6144) return {1, 1, K >= 8192 ? 16 : 8};
-    if (M <= 4) return {1, 1, N >= 16384 && K < 16384 ? 4 : 8};
-    if (N < 16384 || K >= 16384) return {1, 2, 16};
-    return K <= 4096 ? KsShape{1, 2, 4} : KsShape{1, 4, 8};
+    if (K <= 256) return {1, 1, 1};
+    if (K < 1024) return {1, 1, N < 16384 ? 4 : 2};
+    if (N < 5120) return {1, 1, K < 5120 ? 8 : 16};
+    const bool eighths = K < 4096 || (K > 6144 && K <= 10240);
+    if (N >= 16384) {
+      if (M <= 4) return {1, 1, K <= 6144 ? 4 : 8};
+      if (K <= 1536) return {1, 1, 4};
+      if (K > 3072 && K <= 4096) return {1, 2, 4};
+      if (K > 4096 && K < 16384 && M > 8 && N >= 28672) return {1, 4, 8};
+      return {1, 2, K < 16384 || K % 16384 == 0 ? 8 : 16};
+    }
+    if (M <= 4) return {1, 1, N >= 10240 || K < 5120 || eighths ? 8 : 16};
+    if (eighths) return {1, N < 10240 ? 2 : 1, 8};
+    return {1, 2, 16};
   }
   auto tiles = [&](int mt, int t) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * t - 1) / (16 * t)); };
   const int four = K <= 1024 ? 192 : 384;
@@ -337,10 +357,13 @@ hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_sca
     return launch_ks<MT, T, P, NB>(a_codes, a_scale, a_zero, w_codes, w_scale, w_colsum, M, N, K, \
                                    log2g, y, ldy, acc_debug, stream)
   switch (gemm_ksplit_form(M, N, K)) {
+    OFFQ_KS(1, 1, 1, 1);
+    OFFQ_KS(1, 1, 2, 4);
     OFFQ_KS(1, 1, 4, 4);
     OFFQ_KS(1, 1, 8, 4);
     OFFQ_KS(1, 1, 16, 2);
     OFFQ_KS(1, 2, 4, 4);
+    OFFQ_KS(1, 2, 8, 2);
     OFFQ_KS(1, 2, 16, 2);
     OFFQ_KS(1, 4, 8, 2);
     OFFQ_KS(2, 1, 8, 4);

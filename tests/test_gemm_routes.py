@@ -58,6 +58,15 @@ def test_ksplit_ends_where_large_tiles_are_faster(M, N, K, g, kernel):
     # short K: the sums of eight or sixteen waves took longer than their one step
     (1280, 1024, 512, 512, 40404), (1280, 1024, 1024, 1024, 40404), (96, 10240, 512, 512, 40404),
     (17, 14336, 256, 256, 20404), (1280, 1024, 2048, 2048, 40408),
+    # the same for decode calls, 1.1 to 1.45 times as long
+    (1, 14336, 128, 128, 10101), (8, 10240, 256, 128, 10101), (16, 10240, 512, 512, 10104),
+    (5, 57344, 768, 256, 10102), (16, 10240, 1024, 128, 10108),
+    # wide outputs, too few waves or too wide tiles, 1.05 to 1.25 times as long
+    (1, 16384, 8192, 8192, 10108), (5, 20480, 8192, 2048, 10208), (16, 18432, 14336, 2048, 10208),
+    (16, 16384, 16384, 2048, 10208),
+    # as they were
+    (16, 28672, 8192, 8192, 10408), (16, 28672, 4096, 128, 10204), (1, 28672, 4096, 128, 10104),
+    (16, 4096, 14336, 128, 10116), (1, 4096, 4096, 128, 10108), (16, 14336, 4096, 512, 10216),
 ])
 def test_ksplit_forms(M, N, K, g, form):
     assert route(M, N, K, g) == ("ksplit", form)

@@ -143,14 +143,18 @@ def test_large_tile_forms(M, N, K, g):
 
 
 @pytest.mark.parametrize("M,N,K,g", [
-    (1, 17, 128, 128), (16, 1000, 1792, 256),              # 16 channels by 8 waves; fewer steps than waves
-    (7, 1030, 8320, 128), (2, 6150, 8192, 2048),           # by 16; M <= 4, wide
-    (4, 16390, 640, 128), (3, 16390, 16384, 8192),         # by 4; by 8 on long rows
-    (16, 6150, 4224, 128), (5, 16400, 16512, 128),         # 32 channels by 16; 129 groups
-    (16, 16390, 1024, 512), (9, 16400, 4608, 512),         # 32 by 4, 64 by 8
+    (1, 17, 128, 128), (9, 30, 256, 256),                  # 16 channels by one wave
+    (3, 16390, 640, 128), (5, 1030, 640, 128),             # by two, by four
+    (16, 1000, 1792, 256), (2, 6150, 8192, 2048),          # by eight
+    (7, 1030, 8320, 128), (4, 5130, 5120, 1024),           # by sixteen
+    (4, 16390, 1280, 128), (3, 16390, 16384, 8192),        # M <= 4, wide: by four; by eight on long rows
+    (16, 6150, 4224, 128), (5, 16400, 16512, 128),         # 32 channels by sixteen; 129 groups
+    (16, 6150, 1024, 512), (9, 16400, 4608, 512),          # 32 by eight
+    (9, 28690, 4608, 512),                                 # 64 by eight
     (16, 6150, 16384, 512), (3, 6160, 20480, 128),         # long rows, 160 groups
     (5, 6150, 16384, 2048),
     (7, 6150, 4224, 128), (5, 16390, 4096, 1024), (9, 16390, 4608, 512),
+    (4, 16390, 640, 128), (16, 16390, 1024, 512),
 ])
 def test_decode_shapes(M, N, K, g):
     """One to sixteen token rows: each split of K and channel tile, ragged."""
