@@ -151,6 +151,7 @@ def test_large_tile_forms(M, N, K, g):
     (16, 6150, 4224, 128), (5, 16400, 16512, 128),         # 32 channels by sixteen; 129 groups
     (16, 6150, 1024, 512), (9, 16400, 4608, 512),          # 32 by eight
     (9, 28690, 4608, 512),                                 # 64 by eight
+    (2, 16384, 8192, 8192),                                # weights read front to back
     (16, 6150, 16384, 512), (3, 6160, 20480, 128),         # long rows, 160 groups
     (5, 6150, 16384, 2048),
     (7, 6150, 4224, 128), (5, 16390, 4096, 1024), (9, 16390, 4608, 512),
