@@ -55,16 +55,16 @@ __global__ __launch_bounds__(64 * P, 2) void w4a4_ksplit_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, kb = lane >> 4;
   // Workgroups of one channel tile (all its token tiles) follow each other on
-  // one XCD, whose L2 then serves the weights to all but the first. Weights of a
-  // power of two of 64 MB and more put the eight XCDs' runs so far apart that they
-  // meet on the same memory channels; with one token tile, which shares nothing,
-  // they are read front to back instead (16 x 16384 x 16384 33.3 -> 29.0 us,
-  // 8 x 32768 x 8192 30.1 -> 25.5).
+  // one XCD, whose L2 then serves the weights to all but the first. Weights of
+  // 64 or 128 MB put the eight XCDs' runs so far apart that they meet on the same
+  // memory channels; with one token tile, which shares nothing, they are read front to
+  // back instead (16 x 16384 x 16384 33.3 -> 29.0 us, 8 x 32768 x 8192 30.1 -> 25.5;
+  // 32 MB 16 x 16384 x 4096 the same, 256 MB 1 x 16384 x 32768 48 -> 56).
   const int tiles_m = (M + 16 * MT - 1) / (16 * MT);
   const int nwg = (int)gridDim.x;
   int L = (int)blockIdx.x;
   const int64_t wbytes = (int64_t)N * (K >> 1);
-  const bool camps = tiles_m == 1 && wbytes >= (64 << 20) && (wbytes & (wbytes - 1)) == 0;
+  const bool camps = tiles_m == 1 && (wbytes == (64 << 20) || wbytes == (128 << 20));
   if ((nwg & 7) == 0 && !camps) L = (L & 7) * (nwg >> 3) + (L >> 3);
   const int m0 = (L % tiles_m) * (16 * MT), n0 = (L / tiles_m) * (16 * T);
   const int ldk = K >> 1;
