@@ -71,7 +71,8 @@ hipError_t launch_w4a4_gemm_fp6(const uint8_t* a_codes, const uint16_t* a_scale,
                                 int64_t N, int64_t K, int log2g, uint16_t* y, int64_t ldy,
                                 int32_t* acc_debug, hipStream_t stream);
 
-// Decode (M <= 16), long rows of 6144 to 16383 channels: K split over 16 waves.
+// Decode (M <= 16), rows of 20480 to 28672 k, 6144 to 10239 (16383) channels: K split
+// over 16 waves.
 bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int log2g);
 hipError_t launch_w4a4_gemv_mfma(const uint8_t* a_codes, const uint16_t* a_scale,
                                  const int16_t* a_zero, const uint8_t* w_codes,

@@ -297,8 +297,9 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //     4.3, by 8 waves 5.0);
 //   narrow outputs 16 channels by 8 waves, by 16 from K = 5120 (16 x 4096 x 4096: 5.2;
 //     1 x 4096 x 14336: 9.2, by 8 waves 10.5; 1 x 1000 x 6144 4.6 / 5.1);
-//   wider ones with M <= 4 the same by 8 waves, below 10240 channels by 16 where that
-//     leaves whole batches (1 x 5120 x 6144 7.4 / 7.8), and by 4 from N = 16384 up to
+//   wider ones with M <= 4 the same by 8 waves (1 x 9216 x 12288 13.6, by 16 waves 15.3),
+//     up to 8192 channels by 16 where that leaves whole batches (1 x 5120 x 6144 7.4 /
+//     7.8), and by 4 from N = 16384 up to
 //     K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves 15.0; 1 x 16384 x 8192 18.5 / 15.4);
 //   with more rows 32 channels by 16 waves (16 x 14336 x 4096: 10.2; 16 channels by 8
 //     waves 11.5), by 8 below K = 4096 and from 6144 to 10240, where 16 have too few
@@ -308,7 +309,8 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //     K = 4096 (16 x 28672 x 4096: 16.6 / 17.4), 64 channels by 8 where rows and
 //     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K = 16384 on
 //     except at its multiples, whose sixteenths are a power of two apart (16 x 20480 x
-//     28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2).
+//     28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2; below 16384 channels and
+//     up to 8 rows 16 channels by 8: 5 x 16368 x 16384 38.5 / 25.2).
 struct KsShape { int mt, t, p; };
 KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
   if (M <= 16) {
@@ -323,8 +325,8 @@ KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
       if (K > 4096 && K < 16384 && M > 8 && N >= 28672) return {1, 4, 8};
       return {1, 2, K < 16384 || K % 16384 == 0 ? 8 : 16};
     }
-    if (M <= 4) return {1, 1, N >= 10240 || K < 5120 || eighths ? 8 : 16};
-    if (eighths) return {1, N < 10240 ? 2 : 1, 8};
+    if (M <= 4) return {1, 1, N > 8192 || K < 5120 || eighths ? 8 : 16};
+    if (eighths || (K % 16384 == 0 && M <= 8 && N >= 10240)) return {1, N < 10240 ? 2 : 1, 8};
     return {1, 2, 16};
   }
   auto tiles = [&](int mt, int t) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * t - 1) / (16 * t)); };

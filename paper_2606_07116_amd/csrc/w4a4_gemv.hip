@@ -236,11 +236,17 @@ __global__ __launch_bounds__(64 * P) void w4a4_gemv_kernel(
 
 }  // namespace
 
-// Long rows of 6144 to 16383 channels: the group parameters' loads ahead of the
-// stream and the two-batch pipeline are worth more there than the general kernel's
-// freer split (us at M = 16: 28672 -> 8192, g = 512: 23.0 against 25.6, g = 128: 28.6 /
-// 29.6). Everywhere else that one is ahead (16384 -> 16384: 29.4 / 22.6; 8192 -> 10240
-// 21.2 / 15.7; 4096 -> 6144 7.4 / 6.7; 3072 -> 1000, four rows: 8.4 / 4.3).
+// Rows of 20480 to 28672 k and from 6144 channels: the group parameters' loads ahead
+// of the stream and the two-batch pipeline are worth more there than the general
+// kernel's freer split. Both sides of each line (us at g = 512, this kernel / the K-split
+// one):
+//   16 x 8192 x 20480 17.7 / 19.9, 16 x 8192 x 28672 23.5 / 25.8 (M = 1: 22.7 / 23.6),
+//   16 x 6144 x 28672 21.2 / 23.7;
+//   K = 16384: 16 x 8192 17.3 / 16.7, 1 x 8192 17.6 / 15.2, 16 x 6144 14.4 / 15.0;
+//   K = 32768: 16 x 8192 32.0 / 28.6, 1 x 6144 24.3 / 22.0;
+//   from N = 10240 to 16383 with more than eight rows and groups of 512 and more: 16 x
+//   10240 x 28672, g = 2048, 37.3 / 40.0, 8 rows 35.0 / 35.2, one row (g = 4096) 33.5 / 28.5,
+//   16 rows at g = 128 51.1 / 44.7.
 bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   // each wave's part of K is a whole number of batches (a part may end inside
   // a group: the group's zero-point term is added once, by the wave holding
@@ -249,7 +255,8 @@ bool gemv_mfma_supported(int64_t M, int64_t N, int64_t K, int log2g) {
   constexpr int64_t batch = (int64_t)P * KSTEP * BATCH;
   // group parameters (dynamic) + the partial sums of the P waves (static)
   const int64_t lds = ((K >> log2g) * (32 + 16 * T) + 16 * T) * 4 + (int64_t)P * 64 * 4 * T * 4;
-  return M <= 16 && N >= 6144 && N < 16384 && K >= 16384 && log2g >= 7 && K % batch == 0 &&
+  const int64_t widest = M > 8 && log2g >= 9 ? 16384 : 10240;
+  return M <= 16 && N >= 6144 && N < widest && K > 16384 && K < 32768 && log2g >= 7 && K % batch == 0 &&
          (K >> log2g) <= GMAX && lds <= 160 * 1024 &&
          32 * (K / 2) < (int64_t(1) << 31) && M * (K / 2) < (int64_t(1) << 31);
 }

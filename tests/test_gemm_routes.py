@@ -63,13 +63,24 @@ def test_ksplit_ends_where_large_tiles_are_faster(M, N, K, g, kernel):
     (5, 57344, 768, 256, 10102), (16, 10240, 1024, 128, 10108),
     # wide outputs, too few waves or too wide tiles, 1.05 to 1.25 times as long
     (1, 16384, 8192, 8192, 10108), (5, 20480, 8192, 2048, 10208), (16, 18432, 14336, 2048, 10208),
-    (16, 16384, 16384, 2048, 10208),
+    (16, 16384, 16384, 2048, 10208), (8, 16368, 16384, 2048, 10108),
     # as they were
     (16, 28672, 8192, 8192, 10408), (16, 28672, 4096, 128, 10204), (1, 28672, 4096, 128, 10104),
     (16, 4096, 14336, 128, 10116), (1, 4096, 4096, 128, 10108), (16, 14336, 4096, 512, 10216),
 ])
 def test_ksplit_forms(M, N, K, g, form):
     assert route(M, N, K, g) == ("ksplit", form)
+
+
+@pytest.mark.parametrize("M,N,K,g,kernel", [
+    (16, 8192, 28672, 512, "gemv"), (16, 6144, 20480, 128, "gemv"), (1, 8192, 24576, 4096, "gemv"),
+    (16, 14336, 28672, 512, "gemv"), (16, 10240, 28672, 128, "ksplit"), (8, 10240, 28672, 512, "ksplit"),
+    # measured slower there by 1.05 to 1.4 times
+    (16, 8192, 16384, 512, "ksplit"), (1, 8192, 32768, 512, "ksplit"), (16, 8192, 32768, 8192, "ksplit"),
+    (1, 10240, 28672, 512, "ksplit"), (16, 14336, 16384, 128, "ksplit"), (16, 6000, 28672, 512, "ksplit"),
+])
+def test_gemv_window(M, N, K, g, kernel):
+    assert route(M, N, K, g)[0] == kernel
 
 
 def _tested():

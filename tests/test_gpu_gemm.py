@@ -152,8 +152,8 @@ def test_large_tile_forms(M, N, K, g):
     (16, 6150, 1024, 512), (9, 16400, 4608, 512),          # 32 by eight
     (9, 28690, 4608, 512),                                 # 64 by eight
     (2, 16384, 8192, 8192),                                # weights read front to back
-    (16, 6150, 16384, 512), (3, 6160, 20480, 128),         # long rows, 160 groups
-    (5, 6150, 16384, 2048),
+    (16, 6150, 20480, 512), (3, 6160, 20480, 128),         # long rows, 160 groups
+    (5, 6150, 20480, 2048), (6, 10250, 16384, 512),
     (7, 6150, 4224, 128), (5, 16390, 4096, 1024), (9, 16390, 4608, 512),
     (4, 16390, 640, 128), (16, 16390, 1024, 512),
 ])
@@ -242,7 +242,7 @@ def test_large_tile_output_row_stride(M, N, K, g):
 
 
 @pytest.mark.parametrize("M,N,K,g", LARGE_TILES + [(2100, 3722, 8192, 8192), (333, 1000, 2048, 128),
-                                                   (9, 1000, 2048, 128), (9, 6150, 16384, 512)])
+                                                   (9, 1000, 2048, 128), (9, 6150, 20480, 512)])
 def test_large_zero_points(M, N, K, g):
     """Zero-points over the whole int16 range and at both its ends: |z colsum| up to
     2^25 in a group of 128 and far beyond with one group, so that a group's term and
