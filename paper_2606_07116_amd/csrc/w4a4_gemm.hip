@@ -331,22 +331,25 @@ hipError_t launch_gemv_plain(const uint8_t* a_codes, const uint16_t* a_scale, co
 
 // Up to how many tiles of 64 x 64 the K-split kernel is the faster for. Its time grows
 // with them, that of one round of large tiles does not, so the line lies where the two
-// meet (us, K-split / large tiles, N = 4096):
-//   g = 128 (M x N x K): 512 x 4096 x 4096, 512 tiles, 24 / 33, 512 x 4096 x 14336
-//     73 / 102; 333 x 6144 x 4096, 576 tiles, 38 / 34, 333 x 6144 x 14336 111 / 103;
-//   short K: 768 x 4096 x 1024, 768 tiles, one group 15.1 / 12.4;
-//   one group or groups of 1024 and more: 640 rows at K = 8192, 640 tiles, 43 / 51;
-//     768 at K = 4096, 768 tiles, 31 / 29, 1024, 1024 tiles, 34 / 29;
-//   groups of 512, which cost the large tiles more folds: 768 rows at K = 14336,
-//     768 tiles, 88 / 101; 850 at K = 4096, 896 tiles, 33.9 / 33.2;
-//   groups of 256, and more groups than the large tiles keep in LDS, most of all: 1024
-//     rows, 1024 tiles: K = 14336, g = 256, 115 / 131; K = 28672, g = 512, 192 / 233;
-//     1000 x 6144 x 4096, g = 256, 1536 tiles, 50 / 47.
+// meet: at the given number of tiles the ratio of the two is 1 in the mean of the
+// shapes measured (us, K-split / large tiles, N = 4096 where not given):
+//   g = 128: 512 x 4096 x 4096, 512 tiles, 24 / 33, 512 x 4096 x 14336 73 / 102; 333 x
+//     6144 x 4096, 576 tiles, 38 / 34, 333 x 6144 x 14336 111 / 103;
+//   one group, or groups of 1024 and more: 768 rows at K = 1024, 768 tiles, 15.1 / 12.4;
+//     700 at K = 8192, 704 tiles, 43 / 52; 768 at K = 4096, 768 tiles, 31 / 29, 1024, 1024
+//     tiles, 34 / 29;
+//   groups of 512, which cost the large tiles more folds: 640 rows at K = 2048, 640
+//     tiles, 19 / 21; 768 at K = 14336, 768 tiles, 88 / 101; 850 at K = 4096, 896 tiles,
+//     33.9 / 33.2; 1000 at K = 8192, 1024 tiles, 58 / 64;
+//   groups of 256, and more groups than the large tiles keep in LDS, most of all: 700
+//     rows at K = 1024, 704 tiles, 15 / 18; 1024 rows, 1024 tiles: K = 14336, g = 256,
+//     115 / 131; K = 28672, g = 512, 192 / 233; 1000 x 6144 x 4096, g = 256, 1536 tiles,
+//     50 / 47.
 static int64_t ksplit_tiles(int64_t K, int log2g) {
-  if (log2g == 7 || K < 2048) return 512;
-  if (log2g == 8 || gemm_grouped_form(K, log2g) == 2) return 1024;
-  if (K < 4096) return 512;
-  return log2g == 9 ? 768 : 640;
+  if (log2g == 7) return 512;
+  if (log2g == 8 || gemm_grouped_form(K, log2g) == 2) return K < 1024 ? 512 : K < 2048 ? 768 : 1024;
+  if (log2g == 9 && K > 512) return K < 2048 ? 512 : K < 4096 ? 768 : K < 8192 ? 896 : 1024;
+  return K < 4096 ? 512 : 704;
 }
 
 GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, int log2g) {

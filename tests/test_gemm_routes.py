@@ -42,12 +42,13 @@ def test_routes(size, expect):
     # one round of large tiles against 896 ... 2048 tiles of 64 x 64: the K-split kernel
     # took 1.1 to 1.5 times as long
     (1024, 4096, 4096, 4096, "i8"), (1024, 4096, 1024, 1024, "i8"), (512, 8192, 512, 512, "i8"),
-    (2048, 2048, 2048, 2048, "i8"), (4096, 1024, 4096, 512, "i8"), (850, 4096, 4096, 512, "i8"),
+    (2048, 2048, 2048, 2048, "i8"), (4096, 1024, 4096, 512, "i8"), (1024, 4096, 4096, 512, "i8"),
     (128, 28672, 512, 512, "i8"),
     # and where it stays ahead
     (333, 4096, 14336, 512, "ksplit"), (512, 4096, 4096, 4096, "ksplit"),
     (768, 4096, 14336, 512, "ksplit"), (1024, 4096, 14336, 256, "ksplit"),
-    (1024, 4096, 28672, 512, "ksplit"), (640, 4096, 8192, 8192, "ksplit"),
+    (1024, 4096, 28672, 512, "ksplit"), (700, 4096, 8192, 8192, "ksplit"),
+    (700, 4096, 1024, 256, "ksplit"), (1000, 4096, 8192, 512, "ksplit"), (640, 4096, 2048, 512, "ksplit"),
     (512, 4096, 4096, 128, "ksplit"), (333, 6144, 4096, 128, "fp6"),
 ])
 def test_ksplit_ends_where_large_tiles_are_faster(M, N, K, g, kernel):
