@@ -62,7 +62,7 @@ hipError_t launch_w4a4_gemm_ksplit(const uint8_t* a_codes, const uint16_t* a_sca
 
 // The 6-bit matrix format: g = 128, or one group per row on the sizes that
 // gemm_fp6_one_group says it is the faster for.
-bool gemm_fp6_one_group(int64_t M, int64_t N);
+bool gemm_fp6_one_group(int64_t M, int64_t N, int64_t K);
 // 0: one group per row, 256 x 256 tiles; 1: g = 128, 256 x 256; 2: g = 128, 128 x 128
 int gemm_fp6_form(int64_t M, int64_t N, int log2g);
 hipError_t launch_w4a4_gemm_fp6(const uint8_t* a_codes, const uint16_t* a_scale,

@@ -365,7 +365,7 @@ GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, int log2g) {
   const bool few = tiles64 <= ksplit_tiles(K, log2g);
   if (few && gemm_ksplit_supported(M, N, K, log2g)) return ksplit;
   if (gemm_tiles_supported(M, N, K, log2g) &&
-      (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N))))
+      (log2g == 7 || ((K >> log2g) == 1 && gemm_fp6_one_group(M, N, K))))
     return {kGemmFp6, gemm_fp6_form(M, N, log2g)};
   if (gemm_grouped_supported(M, N, K, log2g)) return {kGemmGrouped, gemm_grouped_form(K, log2g)};
   return {kGemmPlain, 0};

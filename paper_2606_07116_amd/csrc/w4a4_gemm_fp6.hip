@@ -430,11 +430,14 @@ bool f6_large(int64_t M, int64_t N) {
 
 }  // namespace
 
-bool gemm_fp6_one_group(int64_t M, int64_t N) {
+bool gemm_fp6_one_group(int64_t M, int64_t N, int64_t K) {
   // One group per row: a round of 256 x 256 tiles takes 1.36 us a stage, one of the
   // i8 kernel's 256 x 128 tiles 1.1 us (4096 x 28672 x 4096 and 2048 x 4096 x 4096).
-  return 5 * ceil_div(ceil_div(M, 256) * ceil_div(N, 256), 256) <
-         4 * ceil_div(ceil_div(M, 256) * ceil_div(N, 128), 256);
+  // With two stages they are the smaller part, and the i8 kernel is ahead (2500 x 8192
+  // x 256 32.5, here 34.6; 2500 x 8192 x 512 37.0 / 37.8).
+  const int64_t f6 = ceil_div(ceil_div(M, 256) * ceil_div(N, 256), 256);
+  const int64_t i8 = ceil_div(ceil_div(M, 256) * ceil_div(N, 128), 256);
+  return K > 256 && 5 * f6 < 4 * i8;
 }
 
 int gemm_fp6_form(int64_t M, int64_t N, int log2g) {

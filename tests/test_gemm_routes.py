@@ -31,7 +31,7 @@ def route(M, N, K, g):
     ((1, 4096, 4096, 64), ("plain_gemv", 0)), ((64, 4096, 4096, 64), ("plain", 0)),
     ((16, 8192, 28672, 512), ("gemv", 0)), ((64, 6144, 4096, 128), ("ksplit", 40208)),
     ((1777, 10240, 8192, 128), ("fp6", 2)), ((4096, 28672, 4096, 128), ("fp6", 1)),
-    ((4096, 28672, 4096, 4096), ("fp6", 0)), ((2048, 4096, 4096, 4096), ("i8", 0, 8)),
+    ((4096, 28672, 4096, 4096), ("fp6", 0)), ((2500, 8192, 256, 256), ("i8", 0, 2)), ((2048, 4096, 4096, 4096), ("i8", 0, 8)),
     ((4096, 4096, 14336, 512), ("i8", 1, 4)), ((4096, 8192, 28672, 512), ("i8", 2, 4)),
 ])
 def test_routes(size, expect):
