@@ -8,20 +8,30 @@
 // Why this format: a 4-bit code c = 0..15 with two zero bits above it is the
 // e2m3 value c / 8 (subnormals up to 7, then the first binade), so unsigned
 // codes enter the matrix cores exactly, at twice the i8 rate, and the products
-// are summed in fp32: multiples of 1/64 below 2^24 / 64, exact for every K
-// here. The accumulators need no conversion before the per-group fold.
+// are summed in fp32: multiples of 1/64, exact while a group's sum stays below
+// 2^24 / 64, which 225 g does up to the largest group (8192). The accumulators
+// need no conversion before the per-group fold.
 //   * Sixteen nibbles become three words of 6-bit fields in eight VALU
 //     operations (expand16; the field order is a permutation of k, the same
 //     for both operands).
 //   * Weight codes are signed: q + 8 goes in, and the excess 8 sum_k q_a comes
 //     out again with the zero-point term, as one fp32 MFMA per group and tile
-//     (k = 2: (asum, 8) and (z, colsum), exact integers in units of 1/64).
+//     (k = 2: (asum, 8) and (z, colsum), integers in units of 1/64). acc - z colsum is
+//     exact while all of it stays below 2^24; where z colsum is larger (|z| above
+//     16384 at g = 128) the sum rounds at 2^-24 of that term, as the fp32 fold of exact
+//     integers does (largest error beyond the bf16 rounding with z over all of int16 and
+//     columns of -8, terms that cancel between groups: 78 units of acc, by that fold 72;
+//     the mean is the same).
 //
-// What bounds it: per stage of 128 k a wave issues 100 (one group) to 170 (g = 128)
-// VALU instructions beside its 8 to 16 matrix instructions, and LDS takes stores at
-// 64 bytes a clock (it returns 128-bit reads at 229): expansion and stores, not the
-// products, take the time, so an operand byte is expanded once per workgroup, on
-// its way into LDS, and the tiles are as large as the registers allow:
+// What bounds it: per stage of 128 k a wave issues 135 (one group, 128 x 64) or 190
+// (g = 128, 64 x 64; 286 for 128 x 64) VALU instructions beside its 12 to 24 matrix
+// instructions, and LDS takes stores at 64 bytes a clock (it returns 128-bit reads at
+// 229). An operand byte is expanded once per workgroup, on its way into LDS, and the
+// tiles are as large as the registers allow. No unit is busy more than half the time
+// (one group, 4096 x 28672 x 4096: matrix cores 38 %, VALU 39 %, LDS 51 %; g = 128, 1777 x
+// 10240 x 8192: 27, 40 and 34 %), and matrix cores and VALU together only 4 to 12 %: with
+// two LDS buffers and one barrier per stage the waves go through the same phase at the
+// same time, and a stage takes nearly the sum of its parts.
 //   * 256 x 256 by eight waves of 128 x 64 (FM = 4): two operand bytes expanded per
 //     256 products. At g = 128 the running sums take 128 registers and each
 //     fragment row is folded right after the next row's reads and expansion were

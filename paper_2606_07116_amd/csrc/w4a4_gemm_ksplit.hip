@@ -11,12 +11,15 @@
 // (no LDS stage, no barrier in the loop): a wave's weight load is one 1 KB
 // block of the blocked layout and its activation load 16 rows of 64 bytes, so
 // every cache line is used whole, and NB steps of 128 k are in flight per
-// wave. The P fp32 partial tiles meet in LDS at the end.
+// wave. The P fp32 partial tiles meet in LDS at the end. What is left is
+// latency: at 333 x 4096 x 14336 (384 tiles of 64 x 64 by four waves, one step in
+// flight, two waves per SIMD) the waves wait 45 % of their cycles, with the matrix
+// cores busy 18 % of the time, the VALU 26 % and the address units 44 %; decode
+// products wait 47 to 64 %, address units 9 to 46 %.
 //
 // Every accumulator holds 16 acc exactly (weight nibbles widened to 16 q);
 // per group F += (s / 16) acc; the zero-point terms are a rank-G product that
-// runs on the fp32 matrix cores after the loop, by the wave that holds a
-// group's first k.
+// runs on the fp32 matrix cores after the loop, a share of the groups per wave.
 #include "common.h"
 #include "gemm_common.h"
 #include "internal.h"
