@@ -46,7 +46,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "W4A4 offset-GEMM int TOPS (prefill) + quantize/decode HBM GB/s vs peak"
-PEAK_INT8_TOPS = 5000.0     # MI355X dense int8 MFMA, 5.0 POP/s
+# MI355X dense matrix rates of the two formats that the products run in: int8, and the
+# 4-bit codes as exact 6-bit floats (e2m3)
+PEAK_TOPS = {"i8": 5000.0, "e2m3": 10100.0}
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, 8 TB/s
 PEAK_FP16_TFLOPS = 2500.0   # MI355X dense fp16 / bf16 MFMA, 2.5 PFLOP/s
 LLC_BYTES = 256 << 20       # MI355X Infinity Cache
@@ -724,7 +726,7 @@ def main():
     tkey = wl if not args.group_size else f"{wl}:g{args.group_size}"
     if wl in ("attn_proj_prefill", "kv_chain"):
         ann_rq(comp["rotate_quantize"], M, K, g)
-        ann_mm(comp["w4a4_gemm"], M, N, K)
+        ann_mm(comp["w4a4_gemm"], M, N, K, g)
         if wl == "kv_chain":
             ann_rq(comp["kv_quantize"], R, Dh, Dh)
         value = work_ops / (ms * 1e-3) / 1e12
@@ -733,8 +735,8 @@ def main():
     elif wl == "mlp_prefill":
         ann_rq(comp["rotate_quantize_up"], up["M"], up["K"], up["g"])
         ann_rq(comp["rotate_quantize_down"], dn["M"], dn["K"], dn["g"])
-        ann_mm(comp["w4a4_gemm_upgate"], up["M"], 2 * up["N"], up["K"])
-        ann_mm(comp["w4a4_gemm_down"], dn["M"], dn["N"], dn["K"])
+        ann_mm(comp["w4a4_gemm_upgate"], up["M"], 2 * up["N"], up["K"], up["g"])
+        ann_mm(comp["w4a4_gemm_down"], dn["M"], dn["N"], dn["K"], dn["g"])
         value = work_ops / (ms * 1e-3) / 1e12
         unit = "TOPS"
         roof = mfma_roof(comp, "w4a4_gemm_upgate", traffic_for(f"w4a4_gemm:{tkey}"))
@@ -767,7 +769,7 @@ def main():
         roof = hbm_roof(comp, name, None)
     elif wl == "prefill_layer":
         for name, (n_, k_) in gemm_shapes.items():
-            ann_mm(comp[name], M, n_, k_)
+            ann_mm(comp[name], M, n_, k_, g)
         ca = comp["kv_attention_prefill"]
         ca["alg_flops"] = attn_flops
         ca["TFLOPs"] = round(attn_flops / (ca["us"] * 1e-6) / 1e12, 1)
@@ -808,7 +810,7 @@ def main():
         "metric": METRIC, "value": round(value, 2), "unit": unit, "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms, 4),
         "higher_is_better": wl != "calibration", "scaling": "weak", "vs_baseline": None,
-        "dtype": "int8",
+        "dtype": "fp6_e2m3 (exact 4-bit codes)" if roof.get("matrix_format") == "e2m3" else "int8",
         "data": "synthetic (seeded Llama-shaped activations with structured outliers; random weights)",
         "config": config, "roofline": roof, "components": comp, "event_gap_us": round(gap, 3),
         "timing": f"us = phase mean over {args.steps} launches with no event between them; "
@@ -936,19 +938,23 @@ def ann_rq(c, M, K, g, n=1):
     ann_bytes(c, rq_bytes(M, K, g) * n)
 
 
-def ann_mm(c, M, N, K):
+def ann_mm(c, M, N, K, g):
+    from paper_2606_07116_amd import _lib
+
     ops = 2.0 * M * N * K
+    c["matrix_format"] = "e2m3" if _lib.gemm_route(M, N, K, g)[0] == "fp6" else "i8"
+    c["peak_TOPS"] = PEAK_TOPS[c["matrix_format"]]
     c["alg_ops"] = ops
     c["TOPS"] = round(ops / (c["us"] * 1e-6) / 1e12, 1)
-    c["frac_int8_peak"] = round(c["TOPS"] / PEAK_INT8_TOPS, 4)
+    c["frac_peak"] = round(c["TOPS"] / c["peak_TOPS"], 4)
     if "median_us" in c:
         c["TOPS_median"] = round(ops / (c["median_us"] * 1e-6) / 1e12, 1)
 
 
 def mfma_roof(comp, dom, traffic):
     c = comp[dom]
-    return {"bound": "mfma", "achieved": c["TOPS"], "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
-            "frac": c["frac_int8_peak"], "traffic": traffic, "kernel": dom,
+    return {"bound": "mfma", "achieved": c["TOPS"], "peak": c["peak_TOPS"], "unit": "TOP/s",
+            "frac": c["frac_peak"], "matrix_format": c["matrix_format"], "traffic": traffic, "kernel": dom,
             "alg_ops_per_launch": c["alg_ops"], "avg_launch_us": c["us"]}
 
 
@@ -987,7 +993,7 @@ def other_configs(torch, offq, _lib, inputs, stream, sp, check, args, n_dist):
     sets, ph = layer("rotate_quantize", "w4a4_gemm", ap, ap["M"], ap["N"])
     comp = measure(ph)
     ann_rq(comp["rotate_quantize"], ap["M"], ap["K"], ap["g"])
-    ann_mm(comp["w4a4_gemm"], ap["M"], ap["N"], ap["K"])
+    ann_mm(comp["w4a4_gemm"], ap["M"], ap["N"], ap["K"], ap["g"])
     for k, t in (("rotate_quantize", "rotate_quantize"), ("w4a4_gemm", "w4a4_gemm")):
         tb = traffic_for(f"{t}:attn_proj_prefill")
         if tb is not None:
@@ -1035,7 +1041,7 @@ def other_configs(torch, offq, _lib, inputs, stream, sp, check, args, n_dist):
     comp = measure([("kv_quantize", kvq)] + ph)
     ann_rq(comp["kv_quantize"], R, Dh, Dh)
     ann_rq(comp["rotate_quantize"], pc["M"], pc["K"], pc["g"])
-    ann_mm(comp["w4a4_gemm"], pc["M"], pc["N"], pc["K"])
+    ann_mm(comp["w4a4_gemm"], pc["M"], pc["N"], pc["K"], pc["g"])
     for k, t in (("kv_quantize", "kv_quantize"), ("rotate_quantize", "rotate_quantize"),
                  ("w4a4_gemm", "w4a4_gemm")):
         tb = traffic_for(f"{t}:kv_chain")

@@ -145,6 +145,20 @@ lib = _load()
 ABI_VERSION = lib.offq_abi_version()
 
 
+class _GemmRoute(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("form", ctypes.c_int32)]
+
+
+def gemm_route(M, N, K, g):
+    """(kernel, form) that a product takes, as csrc/internal.h names them: for tests and
+    for reporting a rate against the matrix format that ran."""
+    fn = lib["_ZN4offq10gemm_routeEllli"]
+    fn.restype = _GemmRoute
+    fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int32]
+    r = fn(M, N, K, g.bit_length() - 1)
+    return ("plain", "plain_gemv", "gemv", "ksplit", "i8", "fp6")[r.kernel], r.form
+
+
 def status_name(status):
     return lib.offq_status_string(int(status)).decode()
 

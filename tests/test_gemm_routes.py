@@ -1,30 +1,15 @@
 """Host-only checks of the product dispatch: which kernel and form a call takes, and
 that the GPU tests run every form that some call takes."""
-import ctypes
-
 import pytest
 
 from paper_2606_07116_amd import _lib
 from tests import test_gpu_gemm as G
 
-I64, I32 = ctypes.c_int64, ctypes.c_int32
-KERNELS = ("plain", "plain_gemv", "gemv", "ksplit", "i8", "fp6")
-
-
-class _Route(ctypes.Structure):
-    _fields_ = [("kernel", I32), ("form", I32)]
-
-
-_fn = ctypes.CDLL(_lib.LIB_PATH)["_ZN4offq10gemm_routeEllli"]
-_fn.restype, _fn.argtypes = _Route, [I64, I64, I64, I32]
-
-
 def route(M, N, K, g):
-    """(kernel, form) as csrc/internal.h names them; the i8 kernel's form with its
-    stages of 128 k per group (8: eight or more)."""
-    r = _fn(M, N, K, g.bit_length() - 1)
-    k = KERNELS[r.kernel]
-    return (k, r.form, min(g // 128, 8)) if k == "i8" else (k, r.form)
+    """The dispatch's (kernel, form); the i8 kernel's form with its stages of 128 k per
+    group (8: eight or more)."""
+    k, form = _lib.gemm_route(M, N, K, g)
+    return (k, form, min(g // 128, 8)) if k == "i8" else (k, form)
 
 
 @pytest.mark.parametrize("size,expect", [
