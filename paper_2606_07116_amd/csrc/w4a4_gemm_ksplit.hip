@@ -305,9 +305,10 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //     7.8), and by 4 from N = 16384 up to
 //     K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves 15.0; 1 x 16384 x 8192 18.5 / 15.4);
 //   with more rows 32 channels by 16 waves (16 x 14336 x 4096: 10.2; 16 channels by 8
-//     waves 11.5), by 8 below K = 4096 and from 6144 to 10240, where 16 have too few
-//     steps (16 x 8192 x 8192 10.2 / 10.9; from N = 10240 16 channels: 5 x 10240 x 1536
-//     4.9 / 5.9);
+//     waves 11.5), by 8 below K = 4096 and, from 6145 channels, from K = 6144 to 10240, where
+//     16 have too few steps (16 x 8192 x 8192 10.2 / 10.9; 16 x 5120 x 8192 stays: 0.98 of
+//     it); there 16 channels where 32 leave 320 to 416 workgroups (5 x 10240 x 1536 4.9,
+//     32 channels 5.4; 16 x 16368 x 2048, 32 channels, 0.91 of it);
 //   from N = 16384 by 8 waves (5 x 20480 x 8192 17.7, 64 channels by 8 20.5), by 4 at
 //     K = 4096 (16 x 28672 x 4096: 16.6 / 17.4), 64 channels by 8 where rows and
 //     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K = 16384 on
@@ -320,7 +321,7 @@ KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
     if (K <= 256) return {1, 1, 1};
     if (K < 1024) return {1, 1, N < 16384 ? 4 : 2};
     if (N < 5120) return {1, 1, K < 5120 ? 8 : 16};
-    const bool eighths = K < 4096 || (K > 6144 && K <= 10240);
+    const bool middle = K > 6144 && K <= 10240;
     if (N >= 16384) {
       if (M <= 4) return {1, 1, K <= 6144 ? 4 : 8};
       if (K <= 1536) return {1, 1, 4};
@@ -328,8 +329,9 @@ KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
       if (K > 4096 && K < 16384 && M > 8 && N >= 28672) return {1, 4, 8};
       return {1, 2, K < 16384 || K % 16384 == 0 ? 8 : 16};
     }
-    if (M <= 4) return {1, 1, N > 8192 || K < 5120 || eighths ? 8 : 16};
-    if (eighths || (K % 16384 == 0 && M <= 8 && N >= 10240)) return {1, N < 10240 ? 2 : 1, 8};
+    if (M <= 4) return {1, 1, N > 8192 || K < 5120 || middle ? 8 : 16};
+    if (K % 16384 == 0 && M <= 8 && N >= 10240) return {1, 1, 8};
+    if (K < 4096 || (middle && N > 6144)) return {1, N >= 10240 && N < 13312 ? 1 : 2, 8};
     return {1, 2, 16};
   }
   auto tiles = [&](int mt, int t) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * t - 1) / (16 * t)); };
