@@ -27,9 +27,9 @@
 // (g = 128, 64 x 64; 286 for 128 x 64) VALU instructions beside its 12 to 24 matrix
 // instructions, and LDS takes stores at 64 bytes a clock (it returns 128-bit reads at
 // 229). An operand byte is expanded once per workgroup, on its way into LDS, and the
-// tiles are as large as the registers allow. No unit is busy more than half the time
+// tiles are as large as the registers allow. No unit is busy more than about half the time
 // (one group, 4096 x 28672 x 4096: matrix cores 38 %, VALU 39 %, LDS 51 %; g = 128, 1777 x
-// 10240 x 8192: 27, 40 and 34 %), and matrix cores and VALU together only 4 to 12 %: with
+// 10240 x 8192: 27, 40 and 34 %), and matrix cores and VALU together only 3 to 12 %: with
 // two LDS buffers and one barrier per stage the waves go through the same phase at the
 // same time, and a stage takes nearly the sum of its parts.
 //   * 256 x 256 by eight waves of 128 x 64 (FM = 4): two operand bytes expanded per
