@@ -311,9 +311,10 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //     32 channels 5.4; 16 x 16368 x 2048, 32 channels, 0.91 of it);
 //   from N = 16384 by 8 waves (5 x 20480 x 8192 17.7, 64 channels by 8 20.5), by 4 at
 //     K = 4096 (16 x 28672 x 4096: 16.6 / 17.4), 64 channels by 8 where rows and
-//     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K = 16384 on
-//     except at its multiples, whose sixteenths are a power of two apart (16 x 20480 x
-//     28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2; below 16384 channels and
+//     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K =
+//     10240 to 13312 (16 x 16384 x 12288 21.5 / 23.2; at 14336 33.1 / 31.4 for 18432
+//     channels) and above 16384 except at its multiples, whose sixteenths are a power of
+//     two apart (16 x 20480 x 28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2; below 16384 channels and
 //     up to 8 rows 16 channels by 8: 5 x 16368 x 16384 38.5 / 25.2).
 struct KsShape { int mt, t, p; };
 KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
@@ -327,7 +328,7 @@ KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
       if (K <= 1536) return {1, 1, 4};
       if (K > 3072 && K <= 4096) return {1, 2, 4};
       if (K > 4096 && K < 16384 && M > 8 && N >= 28672) return {1, 4, 8};
-      return {1, 2, K < 16384 || K % 16384 == 0 ? 8 : 16};
+      return {1, 2, (K > 10240 && K < 13312) || (K > 16384 && K % 16384 != 0) ? 16 : 8};
     }
     if (M <= 4) return {1, 1, N > 8192 || K < 5120 || middle ? 8 : 16};
     if (K % 16384 == 0 && M <= 8 && N >= 10240) return {1, 1, 8};

@@ -50,7 +50,7 @@ def test_ksplit_ends_where_large_tiles_are_faster(M, N, K, g, kernel):
     # wide outputs, too few waves or too wide tiles, 1.05 to 1.25 times as long
     (1, 16384, 8192, 8192, 10108), (5, 20480, 8192, 2048, 10208), (16, 18432, 14336, 2048, 10208),
     (16, 16384, 16384, 2048, 10208), (8, 16368, 16384, 2048, 10108),
-    (16, 14336, 8192, 128, 10208), (16, 10240, 8192, 128, 10108), (8, 6144, 8192, 128, 10216),
+    (16, 16384, 12288, 512, 10216), (16, 28672, 12288, 512, 10408), (16, 14336, 8192, 128, 10208), (16, 10240, 8192, 128, 10108), (8, 6144, 8192, 128, 10216),
     # as they were
     (16, 28672, 8192, 8192, 10408), (16, 28672, 4096, 128, 10204), (1, 28672, 4096, 128, 10104),
     (16, 4096, 14336, 128, 10116), (1, 4096, 4096, 128, 10108), (16, 14336, 4096, 512, 10216),
