@@ -280,7 +280,8 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 }
 
 // Tile and split, from sweeps over M = 17 ... 1000, N = 1000 ... 28672, K = 4096 ... 14336
-// (us, best of eighteen shapes). The kernel wants about 256 workgroups of
+// (us of the product alone, weights cycled beyond the 256 MB last-level cache; best of
+// eighteen shapes). The kernel wants about 256 workgroups of
 // eight waves or 384 of four; larger tiles reload less, more parts of K fill
 // the chip where the output is small:
 //   64 x 64 tiles by 4 waves from 384 tiles (64 x 28672 x 4096: 27.0, by 8 waves 32.0;
