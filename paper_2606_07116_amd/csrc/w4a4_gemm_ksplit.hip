@@ -296,15 +296,13 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 // Up to 16 rows the weights' stream bounds it, and waves in flight (per byte) carry
 // it; the activations are read again by every channel tile, which counts from about
 // five rows. Sweeps over M = 1 ... 16, N = 64 ... 57344, K = 128 ... 32768:
-//   a wave per two to four steps of a short K: more of them only add to the reduction
-//     (8 x 10240 x 128 2.8, by 16 waves 4.7; 5 x 10240 x 512 3.9 / 5.1; 1 x 14336 x 768
+//   one to four waves for a short K: more of them only add to the reduction (8 x 10240 x 128 2.8, by 16 waves 4.7; 5 x 10240 x 512 3.9 / 5.1; 1 x 14336 x 768
 //     4.3, by 8 waves 5.0);
 //   narrow outputs 16 channels by 8 waves, by 16 from K = 5120 (16 x 4096 x 4096: 5.2;
 //     1 x 4096 x 14336: 9.2, by 8 waves 10.5; 1 x 1000 x 6144 4.6 / 5.1);
 //   wider ones with M <= 4 the same by 8 waves (1 x 9216 x 12288 13.6, by 16 waves 15.3),
 //     up to 8192 channels by 16 where that leaves whole batches (1 x 5120 x 6144 7.4 /
-//     7.8), and by 4 from N = 16384 up to
-//     K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves 15.0; 1 x 16384 x 8192 18.5 / 15.4);
+//     7.8), and by 4 from N = 16384 up to K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves 15.0; 1 x 16384 x 8192 18.5 / 15.4);
 //   with more rows 32 channels by 16 waves (16 x 14336 x 4096: 10.2; 16 channels by 8
 //     waves 11.5), by 8 below K = 4096 and, from 6145 channels, from K = 6144 to 10240, where
 //     16 have too few steps (16 x 8192 x 8192 10.2 / 10.9; 16 x 5120 x 8192 stays: 0.98 of
@@ -312,11 +310,11 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 //     32 channels 5.4; 16 x 16368 x 2048, 32 channels, 0.91 of it);
 //   from N = 16384 by 8 waves (5 x 20480 x 8192 17.7, 64 channels by 8 20.5), by 4 at
 //     K = 4096 (16 x 28672 x 4096: 16.6 / 17.4), 64 channels by 8 where rows and
-//     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K =
-//     10240 to 13312 (16 x 16384 x 12288 21.5 / 23.2; at 14336 33.1 / 31.4 for 18432
-//     channels) and above 16384 except at its multiples, whose sixteenths are a power of
-//     two apart (16 x 20480 x 28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2; below 16384 channels and
-//     up to 8 rows 16 channels by 8: 5 x 16368 x 16384 38.5 / 25.2).
+//     channels are most (16 x 28672 x 8192: 24.4 / 25.9), and 16 from K = 10240 to 13312
+//     (16 x 16384 x 12288 21.5 / 23.2; at 14336 33.1 / 31.4 for 18432 channels) and above
+//     16384 except at its multiples, whose sixteenths are a power of two apart (16 x
+//     20480 x 28672 64 / 66; 16 x 16384 x 16384 36.8, by 8 waves 33.2; below 16384
+//     channels and up to 8 rows 16 channels by 8: 5 x 16368 x 16384 38.5 / 25.2).
 struct KsShape { int mt, t, p; };
 KsShape ks_shape(int64_t M, int64_t N, int64_t K) {
   if (M <= 16) {
