@@ -296,13 +296,15 @@ hipError_t launch_ks(const uint8_t* a_codes, const uint16_t* a_scale, const int1
 // Up to 16 rows the weights' stream bounds it, and waves in flight (per byte) carry
 // it; the activations are read again by every channel tile, which counts from about
 // five rows. Sweeps over M = 1 ... 16, N = 64 ... 57344, K = 128 ... 32768:
-//   one to four waves for a short K: more of them only add to the reduction (8 x 10240 x 128 2.8, by 16 waves 4.7; 5 x 10240 x 512 3.9 / 5.1; 1 x 14336 x 768
-//     4.3, by 8 waves 5.0);
+//   one to four waves for a short K: more of them only add to the reduction (8 x 10240 x
+//     128 2.8, by 16 waves 4.7; 5 x 10240 x 512 3.9 / 5.1; 1 x 14336 x 768 4.3, by 8 waves
+//     5.0);
 //   narrow outputs 16 channels by 8 waves, by 16 from K = 5120 (16 x 4096 x 4096: 5.2;
 //     1 x 4096 x 14336: 9.2, by 8 waves 10.5; 1 x 1000 x 6144 4.6 / 5.1);
 //   wider ones with M <= 4 the same by 8 waves (1 x 9216 x 12288 13.6, by 16 waves 15.3),
 //     up to 8192 channels by 16 where that leaves whole batches (1 x 5120 x 6144 7.4 /
-//     7.8), and by 4 from N = 16384 up to K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves 15.0; 1 x 16384 x 8192 18.5 / 15.4);
+//     7.8), and by 4 from N = 16384 up to K = 6144 (1 x 28672 x 4096: 13.5, by 8 waves
+//     15.0; 1 x 16384 x 8192 18.5 / 15.4);
 //   with more rows 32 channels by 16 waves (16 x 14336 x 4096: 10.2; 16 channels by 8
 //     waves 11.5), by 8 below K = 4096 and, from 6145 channels, from K = 6144 to 10240, where
 //     16 have too few steps (16 x 8192 x 8192 10.2 / 10.9; 16 x 5120 x 8192 stays: 0.98 of
